@@ -335,6 +335,10 @@ template <typename R> struct Engine {
     const SweepPlan *gplan = nullptr;
     char *gscratch = nullptr;
     size_t gscratch_bytes = 0;
+    // the gates from aplan_from on as tile passes (nullptr: one kernel per gate);
+    // shares the gradient's scratch, which is free until the reverse sweep
+    const SweepPlan *aplan = nullptr;
+    int aplan_from = 0;
     int reg_mode = REG_F32;
     bool stepped = false;     // one kernel per sweep step (circuits the fused passes do not take)
 
@@ -516,8 +520,13 @@ template <typename R> struct Engine {
     void finish_energy_grad(int pos, bool want_grad, void *psi_copy_c128) {
         const Circuit &c = pb.circ;
         void *psi = state(0), *lam = state(1);
+        bool negated = false;
+        if (aplan && pos == aplan_from) {
+            negated = run_fused_apply<R>(*aplan, c, pb.fwd, pos, psi, gscratch, gscratch_bytes, st, &ctx->stats);
+            pos = c.M;
+        }
         for (; pos < c.M; ++pos) apply(pos, false, psi, nullptr);
-        if (psi_copy_c128) { ++ctx->stats.other_launches; launch_to_c128<R>(psi, psi_copy_c128, n, st); }
+        if (psi_copy_c128) { ++ctx->stats.other_launches; launch_to_c128<R>(psi, psi_copy_c128, n, negated, st); }
         energy(psi, lam);
         if (!want_grad || c.P == 0) return;
         if (gplan) {
@@ -630,6 +639,12 @@ void unpack_to_params(const Problem &pb, const double *lraw, const double *traw,
     launch_contract_metric(gout, tout, c.P, param_map_dev + c.P, param_map_dev + c.P + c.NP + 1, c.NP, G, T, st);
 }
 
+// Fewest gates the forward pass runs as tile passes: a gate's own launch is
+// about 3 us on a small register, a plan's one upload with its wait and a pass
+// about 25 us (the 9 gates behind the metric of the 10-qubit step: 955 us a
+// step gate by gate, 931 us in one pass; below 8 the launches win).
+constexpr int kMinFusedApply = 8;
+
 struct CallResult {
     // device pointers into the workspace
     double *G = nullptr, *T = nullptr, *graw = nullptr, *eraw = nullptr;
@@ -704,6 +719,17 @@ CallResult run(qng_ctx *ctx, const Problem &pb, const CallSpec &spec) {
         gplan = ctx->sweep_cache.get_gradient(c, ctx->opt_tile, (int)amp, f64_regs);
         scratch = std::max(scratch, fused_gradient_scratch_bytes(*gplan, c.M));
     }
+    // the forward pass to psi (after a metric: the gates behind its last
+    // rotation) in tile passes where that saves launches, i.e. passes over the
+    // register
+    std::shared_ptr<const SweepPlan> aplan;
+    const int aplan_from = spec.metric && c.P ? c.rots[c.P - 1].pos : 0;
+    const size_t scratch_without_apply = scratch;
+    if (ctx->opt_fusion != 0 && !c.has_strings && !spec.psi_final_dev && (spec.grad || spec.psi_out_dev) &&
+        c.M - aplan_from >= kMinFusedApply) {
+        aplan = ctx->sweep_cache.get_apply(c, aplan_from, ctx->opt_tile, (int)amp);
+        scratch = std::max(scratch, fused_apply_scratch_bytes(*aplan, c.M));
+    }
     // circuits the fused passes do not take: one kernel per sweep step, with up
     // to kStepMaxPhi columns per lambda sweep as memory allows (half of what is
     // free, and the context's limit)
@@ -722,6 +748,14 @@ CallResult run(qng_ctx *ctx, const Problem &pb, const CallSpec &spec) {
     }
     Layout L = plan_layout(n, c.P, param_map_ints(c), amp, n_states, spec.in_host != nullptr, scratch,
                            spec.device_solve ? c.NP : -1);
+    const size_t cap_ws = ctx->fixed_ws ? ctx->fixed_ws_bytes : ctx->mem_limit;
+    if (aplan && cap_ws && L.total > cap_ws) {
+        // the plan's image is all that does not fit: one kernel per gate needs none
+        aplan.reset();
+        scratch = scratch_without_apply;
+        L = plan_layout(n, c.P, param_map_ints(c), amp, n_states, spec.in_host != nullptr, scratch,
+                        spec.device_solve ? c.NP : -1);
+    }
     char *base = ensure_workspace(ctx, L.total);
     hipStream_t st = ctx->stream;
     char *sb = base + L.states;
@@ -730,10 +764,12 @@ CallResult run(qng_ctx *ctx, const Problem &pb, const CallSpec &spec) {
                 (double *)(base + L.graw), (double *)(base + L.eraw));
     if (gplan) {
         e.gplan = gplan.get();
-        e.gscratch = base + L.sweep;
-        e.gscratch_bytes = L.sweep_bytes;
         e.reg_mode = sweep_reg_mode(ctx, amp);
     }
+    e.aplan = aplan.get();
+    e.aplan_from = aplan_from;
+    e.gscratch = base + L.sweep;
+    e.gscratch_bytes = L.sweep_bytes;
     e.stepped = stepped;
 
     const void *in_c128 = spec.in_dev;
@@ -1740,7 +1776,7 @@ qng_status qng_energy_dev(qng_ctx *ctx, const qng_circuit *circ, const void *in_
         validate_hamiltonian(circ, ham);
         if (!E_dev || !psi_dev) fail(QNG_E_INVALID_ARG, "output is NULL");
         reset_stats(ctx);
-        Problem pb = make_problem(circ, theta, ham);
+        Problem pb = make_problem(circ, theta, ham, ctx->opt_fusion != 0);
         dispatch(prec, [&](auto tag) {
             using R = decltype(tag);
             CallSpec spec;

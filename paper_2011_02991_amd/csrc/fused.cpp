@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <string>
 
 #include "fused.hpp"
@@ -636,6 +637,78 @@ int run_states_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &
     }
     return pos;
 }
+
+size_t fused_apply_scratch_bytes(const SweepPlan &a, int M) {
+    size_t b = 0;
+    b += align256((size_t)M * 64 + 64);
+    b += align256(a.dev_passes.size() * sizeof(DevPass) + 64);
+    b += align256(a.dev_ops.size() * sizeof(DevOp) + 64);
+    b += align256(a.dev_maps.size() * sizeof(DevMap) + 64);
+    b += align256(a.dev_passes.size() * sizeof(LaunchItem) + 64);
+    return b;
+}
+
+template <typename R>
+bool run_fused_apply(const SweepPlan &a, const Circuit &c, const std::vector<Mat2> &fwd, int from, void *psi,
+                     char *scratch, size_t scratch_bytes, hipStream_t st, qng_stats *stats) {
+    if (a.cols.empty()) return false;
+    if (fused_apply_scratch_bytes(a, c.M) > scratch_bytes)
+        fail(QNG_E_DEVICE, "fused apply: scratch too small (internal)");
+    const uint32_t tiles = 1u << (c.n - a.m);
+    // the gates' own shears and plane rotations, in the register's precision
+    std::vector<R> mats((size_t)c.M * 8, (R)0);
+    bool negated = false;
+    for (int pos = from; pos < c.M; ++pos) {
+        const int kind = c.gates[pos].kind;
+        if (kind == QNG_CNOT || kind == QNG_CZ) continue;
+        R *o = &mats[(size_t)pos * 8];
+        if (kind <= QNG_RZ) {
+            const Shear sh = adjoint_shear(kind == QNG_RX ? AX_X : kind == QNG_RY ? AX_Y : AX_Z, fwd[pos]);
+            o[0] = (R)sh.u;
+            o[1] = (R)sh.w;
+            negated ^= fwd[pos].a.real() < 0;
+        } else {
+            const PlaneRot pl = adjoint_plane(kind == QNG_CRX ? AX_X : kind == QNG_CRY ? AX_Y : AX_Z, fwd[pos]);
+            o[2] = (R)pl.c;
+            o[3] = (R)pl.s;
+        }
+    }
+    std::vector<LaunchItem> items;
+    for (size_t t = 0; t < a.dev_passes.size(); ++t) {
+        LaunchItem it{};
+        it.pass = (uint32_t)t;
+        it.ntiles = tiles;
+        it.regA = psi;
+        items.push_back(it);
+    }
+    // one upload: the table, the plan and the items in one image
+    std::vector<char> image;
+    auto put = [&](const void *src, size_t bytes) {
+        const size_t off = image.size();
+        image.resize(off + align256(bytes + 64));
+        if (bytes) std::memcpy(image.data() + off, src, bytes);
+        return scratch + off;
+    };
+    image.reserve(fused_apply_scratch_bytes(a, c.M));
+    const char *d_mats = put(mats.data(), mats.size() * sizeof(R));
+    DevPass *d_passes = (DevPass *)put(a.dev_passes.data(), a.dev_passes.size() * sizeof(DevPass));
+    DevOp *d_ops = (DevOp *)put(a.dev_ops.data(), a.dev_ops.size() * sizeof(DevOp));
+    DevMap *d_maps = (DevMap *)put(a.dev_maps.data(), a.dev_maps.size() * sizeof(DevMap));
+    LaunchItem *d_items = (LaunchItem *)put(items.data(), items.size() * sizeof(LaunchItem));
+    FCHECK(hipMemcpyAsync(scratch, image.data(), image.size(), hipMemcpyHostToDevice, st));
+    FCHECK(hipStreamSynchronize(st));   // the image is released at return
+    for (size_t t = 0; t < items.size(); ++t) {
+        launch_sweep_pass_states<R>(d_items + t, 1, tiles, d_passes, d_ops, d_maps, (const double *)d_mats,
+                                    (const float *)d_mats, a.m, a.rb, 0, st, a.ctrl);
+        ++stats->other_launches;
+    }
+    return negated;
+}
+
+template bool run_fused_apply<double>(const SweepPlan &, const Circuit &, const std::vector<Mat2> &, int, void *, char *,
+                                      size_t, hipStream_t, qng_stats *);
+template bool run_fused_apply<float>(const SweepPlan &, const Circuit &, const std::vector<Mat2> &, int, void *, char *,
+                                     size_t, hipStream_t, qng_stats *);
 
 size_t fused_gradient_scratch_bytes(const SweepPlan &g, int M) {
     size_t b = 0;

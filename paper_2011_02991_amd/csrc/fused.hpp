@@ -79,6 +79,15 @@ int run_states_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &
                       const std::function<void()> &restart, hipStream_t st, qng_stats *stats, bool profile,
                       bool real_products);
 
+size_t fused_apply_scratch_bytes(const SweepPlan &a, int M);
+
+// psi <- the gates of the plan a (build_apply_plan) in tile passes.  Rotations
+// with cos(theta/2) < 0 are applied negated; returns true when that leaves psi
+// negated (E and the gradient are quadratic in psi and do not see it).
+template <typename R>
+bool run_fused_apply(const SweepPlan &a, const Circuit &c, const std::vector<Mat2> &fwd, int from, void *psi,
+                     char *scratch, size_t scratch_bytes, hipStream_t st, qng_stats *stats);
+
 size_t fused_gradient_scratch_bytes(const SweepPlan &g, int M);
 
 // Reverse sweep of the energy gradient through the fused passes of the

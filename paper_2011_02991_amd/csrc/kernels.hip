@@ -93,11 +93,12 @@ __global__ void k_init_state(typename Cplx<R>::T *dst, uint64_t dim, const doubl
     }
 }
 
+// sign: +1, or -1 for a register that holds -psi
 template <typename R>
-__global__ void k_to_c128(const typename Cplx<R>::T *src, double2 *dst, uint64_t dim) {
+__global__ void k_to_c128(const typename Cplx<R>::T *src, double2 *dst, uint64_t dim, double sign) {
     for (uint64_t x = blockIdx.x * (uint64_t)kBlock + threadIdx.x; x < dim; x += (uint64_t)gridDim.x * kBlock) {
         const typename Cplx<R>::T v = src[x];
-        dst[x] = make_double2((double)v.x, (double)v.y);
+        dst[x] = make_double2(sign * (double)v.x, sign * (double)v.y);
     }
 }
 
@@ -954,10 +955,10 @@ template <typename R> void launch_init_state(void *dst, int n, const void *src, 
     check_launch();
 }
 
-template <typename R> void launch_to_c128(const void *src, void *dst, int n, hipStream_t st) {
+template <typename R> void launch_to_c128(const void *src, void *dst, int n, bool negate, hipStream_t st) {
     const uint64_t dim = uint64_t(1) << n;
     hipLaunchKernelGGL(k_to_c128<R>, dim3(grid_for(dim)), dim3(kBlock), 0, st,
-                       (const typename Cplx<R>::T *)src, (double2 *)dst, dim);
+                       (const typename Cplx<R>::T *)src, (double2 *)dst, dim, negate ? -1.0 : 1.0);
     check_launch();
 }
 
@@ -1243,7 +1244,7 @@ void launch_grad_from_raw(const double *graw, const int *param_of, int P, double
 
 #define QNG_INSTANTIATE(R)                                                                                        \
     template void launch_init_state<R>(void *, int, const void *, hipStream_t);                                  \
-    template void launch_to_c128<R>(const void *, void *, int, hipStream_t);                                      \
+    template void launch_to_c128<R>(const void *, void *, int, bool, hipStream_t);                                \
     template void launch_copy<R>(const void *, void *, int, hipStream_t);                                         \
     template void launch_apply_1q<R>(void *, void *, int, int, const DevMat2 &, hipStream_t);                     \
     template void launch_apply_1q_tab<R>(void *, void *, int, int, const double *, hipStream_t);                  \

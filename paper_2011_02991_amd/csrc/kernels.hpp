@@ -54,7 +54,7 @@ void launch_sweep_step(const StepRegs &regs, const StepGate &g, double *partials
 template <typename R> void launch_fixed_multi(const StepRegs &regs, int n, bool cnot, int a, int b, hipStream_t st);
 
 template <typename R> void launch_init_state(void *dst, int n, const void *src_c128, hipStream_t st);
-template <typename R> void launch_to_c128(const void *src, void *dst, int n, hipStream_t st);
+template <typename R> void launch_to_c128(const void *src, void *dst, int n, bool negate, hipStream_t st);
 template <typename R> void launch_copy(const void *src, void *dst, int n, hipStream_t st);
 
 // Apply a 2x2 matrix on qubit q to one register (s1 == nullptr) or to two.

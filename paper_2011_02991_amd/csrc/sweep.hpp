@@ -261,6 +261,10 @@ int default_tile_qubits(int n, int amp_bytes, bool reg_f64);
 // <lambda|sigma_r|phi> of rotation r goes to destination r.
 SweepPlan build_gradient_plan(const Circuit &c, int tile_qubits, int amp_bytes, bool reg_f64);
 
+// Plan of the gates at positions [from, M) applied in order to one register (a
+// plan of width 0 with one column; its gate table holds the gates themselves).
+SweepPlan build_apply_plan(const Circuit &c, int from, int tile_qubits, int amp_bytes);
+
 struct SweepCache {
     std::map<std::vector<int32_t>, std::shared_ptr<SweepPlan>> plans;
     const SweepPlan &get(const Circuit &c, int tile_qubits, int amp_bytes, int small, bool reg_f64, int width = 1,
@@ -273,6 +277,7 @@ struct SweepCache {
                                                 bool reg_f64, int width = 1,
                                                 const std::vector<int> *rot_block = nullptr);
     std::shared_ptr<const SweepPlan> get_gradient(const Circuit &c, int tile_qubits, int amp_bytes, bool reg_f64);
+    std::shared_ptr<const SweepPlan> get_apply(const Circuit &c, int from, int tile_qubits, int amp_bytes);
 };
 
 // Structure key of a circuit (gate kinds, qubits, which gates are rotations).

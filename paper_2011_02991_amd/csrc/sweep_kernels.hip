@@ -1397,11 +1397,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
                 if (h2 & crot_bits(3)) crot_handlers<3, RB, T, CT, W>(x, h2, on, c, s, sink, red, slot, fa, tid);
                 if (h2 & (h2bit(HB2_CDIAG) | h2bit(HB2_PRODCDIAG) | h2bit(HB2_PRODCZ))) {
                     const uint32_t one = loc_mask<T>(op.b0(), op.q0(), tid, base);
-                    if (!kNoProducts && (h2 & (h2bit(HB2_PRODCDIAG) | h2bit(HB2_PRODCZ)))) {
-                        const Regs<CT, T, W> y = masked_lambda<T, CT, W>(x, on, one);
-                        double pr[W], pi[W];
-                        prodw_plain<T, CT, W>(y, pr, pi);
-                        row_reduce_store<W>(sink, red, slot, fa, tid, pr, pi);
+                    if constexpr (!kNoProducts) {
+                        if (h2 & (h2bit(HB2_PRODCDIAG) | h2bit(HB2_PRODCZ))) {
+                            const Regs<CT, T, W> y = masked_lambda<T, CT, W>(x, on, one);
+                            double pr[W], pi[W];
+                            prodw_plain<T, CT, W>(y, pr, pi);
+                            row_reduce_store<W>(sink, red, slot, fa, tid, pr, pi);
+                        }
                     }
                     if (h2 & (h2bit(HB2_CDIAG) | h2bit(HB2_PRODCDIAG))) cdiag<T, CT, W>(x, on, one, c, s);
                 }
@@ -1581,15 +1583,13 @@ void launch_rb(const LaunchItem *items, int n_items, uint32_t total_tiles, const
     if (width == 0) {
         // lambda alone (forward plans), passes without products only
         if constexpr (kNoProducts) {
-            if (!ctrl) {
-                if (full)
-                    launch_full<R, CT, RB, true, 0, false>(items, n_items, total_tiles, passes, ops, maps, mats,
-                                                           partials, m, st);
-                else
-                    launch_full<R, CT, RB, false, 0, false>(items, n_items, total_tiles, passes, ops, maps, mats,
-                                                            partials, m, st);
-                return;
-            }
+            if (full)
+                launch_ctrl<R, CT, RB, true, 0>(items, n_items, total_tiles, passes, ops, maps, mats, partials, m,
+                                                ctrl, st);
+            else
+                launch_ctrl<R, CT, RB, false, 0>(items, n_items, total_tiles, passes, ops, maps, mats, partials, m,
+                                                 ctrl, st);
+            return;
         }
         throw hipErrorInvalidValue;
     }
@@ -1633,9 +1633,16 @@ void launch_ct(const LaunchItem *items, int n_items, uint32_t total_tiles, const
         // FP64 registers stop at 8 amplitudes per thread: at 16 the kernel
         // needs 178-226 VGPRs (two waves per SIMD) and measured 1.8-2.2x slower
         // per pass at n = 26
+        // (lambda alone has the room: 16 FP64 amplitudes are 64 VGPRs)
         if constexpr (sizeof(CT) == 4) {
             launch_rb<R, CT, 4>(items, n_items, total_tiles, passes, ops, maps, mats, partials, m, width, ctrl, st);
             break;
+        } else if constexpr (kNoProducts) {
+            if (width == 0 && m - 4 == 8) {
+                launch_ctrl<R, CT, 4, true, 0>(items, n_items, total_tiles, passes, ops, maps, mats, partials, m,
+                                               ctrl, st);
+                break;
+            }
         }
         [[fallthrough]];
     default: throw hipErrorInvalidValue;
