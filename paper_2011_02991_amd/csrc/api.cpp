@@ -590,6 +590,7 @@ struct CallSpec {
     const void *psi_final_dev = nullptr;  // gradient from a given final state (nullable)
     bool real_products = false;           // fused metric: real parts of L only (the caller needs Re G)
     bool device_solve = false;            // reserve the workspace of the step's device solve
+    bool solve_optional = false;          // ... unless the workspace limit leaves no room for it
 };
 
 // Columns per lambda sweep of the fused metric.  Blocks of two columns need
@@ -653,7 +654,7 @@ struct CallResult {
 };
 
 template <typename R>
-CallResult run(qng_ctx *ctx, const Problem &pb, const CallSpec &spec) {
+CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
     const Circuit &c = pb.circ;
     const int n = c.n;
     const size_t amp = 2 * sizeof(R);
@@ -755,6 +756,10 @@ CallResult run(qng_ctx *ctx, const Problem &pb, const CallSpec &spec) {
         scratch = scratch_without_apply;
         L = plan_layout(n, c.P, param_map_ints(c), amp, n_states, spec.in_host != nullptr, scratch,
                         spec.device_solve ? c.NP : -1);
+    }
+    if (spec.solve_optional && cap_ws && L.total > cap_ws) {
+        spec.device_solve = false;
+        L = plan_layout(n, c.P, param_map_ints(c), amp, n_states, spec.in_host != nullptr, scratch, -1);
     }
     char *base = ensure_workspace(ctx, L.total);
     hipStream_t st = ctx->stream;
@@ -880,6 +885,27 @@ void device_grad(const CallResult &r, const Problem &pb, double *grad, hipStream
     else launch_grad_contract(r.graw, r.param_of + P, r.param_of + P + pb.circ.NP + 1, pb.circ.NP, grad, st);
 }
 
+// Whether a host step's systems (sum of their NP^3) are solved on the device.
+// One system, with its copies back: 128 parameters 0.150 ms on the device, 0.093
+// on the host and 0.03-0.05 for bringing G there; 192: 0.207 against 0.305; 80:
+// 0.119 against 0.028; 432: 0.433 against 3.99.  The systems of a batch share
+// the device's launches, so their host times add up against one chain.
+inline bool solve_on_device(double sum_np3) { return sum_np3 >= 128.0 * 128.0 * 128.0; }
+
+// The step's solve in its workspace: A with the right-hand side's row
+// ((NP + 1) * NP), then x and grad (NP each) and the status word.
+SolveItem solve_item(const double *G, char *solve, int NP) {
+    SolveItem s{};
+    s.G = G;
+    s.P = NP;
+    s.A = (double *)solve;
+    s.x = s.A + (size_t)(NP + 1) * NP;
+    s.grad = s.x + NP;
+    s.status = (int32_t *)(s.x + 2 * (size_t)NP);
+    return s;
+}
+SolveItem solve_item(const CallResult &r, int NP) { return solve_item(r.G, r.solve, NP); }
+
 // qng_energy_grad_dev and its variant on the fixed scratch: E and grad E in
 // device memory, asynchronous on the context's stream.
 void energy_grad_dev_call(qng_ctx *ctx, const qng_circuit *circ, const void *in_state_dev, const qng_pauli_sum *ham,
@@ -914,6 +940,11 @@ int member_tile(const Circuit &c, int opt_tile, int amp, bool f64) {
 
 struct BatchLayout {
     std::vector<size_t> psi, traw, graw, gout, tout, param_of, lraw_class;
+    // device solves (none when they do not fit): per member A, and x, grad and
+    // the status word of all members one after another (xg_off: in doubles)
+    std::vector<size_t> solve_a, xg_off;
+    size_t xg = 0, xg_doubles = 0, solve_items = 0;
+    bool device_solve = false;
     size_t lam = 0, staging = 0, partials = 0, eraw = 0, gscratch = 0, gscratch_bytes = 0;
     size_t scratch = 0, images = 0, arena = 0, spart = 0, fwd = 0, adj = 0, adj32 = 0;
     size_t total = 0;
@@ -1029,6 +1060,18 @@ BatchRun batch_metric(qng_ctx *ctx, const std::vector<Problem> &pbs, const doubl
     L.adj = take(mats);
     L.adj32 = take(mats / 2);
     L.total = off;
+    double np3 = 0;
+    for (int b = 0; b < B; ++b) {
+        const size_t NP = pbs[b].circ.NP;
+        np3 += (double)NP * NP * NP;
+        L.solve_a.push_back(take((NP + 1) * NP * 8));
+        L.xg_off.push_back(L.xg_doubles);
+        L.xg_doubles += 2 * NP + 1;
+    }
+    L.xg = take(L.xg_doubles * 8);
+    L.solve_items = take((size_t)B * sizeof(SolveItem));
+    L.device_solve = solve_on_device(np3) && (!ctx->mem_limit || off <= ctx->mem_limit);
+    if (L.device_solve) L.total = off;
     char *base = ensure_workspace(ctx, L.total);
     run.base = base;
 
@@ -1586,7 +1629,8 @@ qng_status qng_step(qng_ctx *ctx, const qng_circuit *circ, const double *in_stat
         Problem pb = make_problem(circ, theta, ham, ctx->opt_fusion != 0);
         apply_metric_settings(ctx, pb);
         const int P = pb.circ.P, NP = pb.circ.NP;
-        std::vector<double> G(2 * (size_t)NP * NP + 2), graw(2 * (size_t)P + 2), e(2), grad(NP + 1);
+        std::vector<double> G, graw(2 * (size_t)P + 2), e(2), grad(NP + 1), x(NP + 1), xg(2 * (size_t)NP + 1);
+        bool solved = false;
         dispatch(prec, [&](auto tag) {
             using R = decltype(tag);
             CallSpec spec;
@@ -1597,21 +1641,44 @@ qng_status qng_step(qng_ctx *ctx, const qng_circuit *circ, const double *in_stat
             // the solve reads Re G only: without a G output, the metric's
             // inner products keep their real parts
             spec.real_products = G_out == nullptr;
+            // the device solves where its workspace fits, so G stays there
+            // unless it is asked for
+            spec.device_solve = spec.solve_optional = solve_on_device((double)NP * NP * NP);
+            hipStream_t st = ctx->stream;
             CallResult r = run<R>(ctx, pb, spec);
-            if (P) {
-                HIPCHECK(hipMemcpyAsync(G.data(), r.G, (size_t)NP * NP * 16, hipMemcpyDeviceToHost, ctx->stream));
-                HIPCHECK(hipMemcpyAsync(graw.data(), r.graw, (size_t)P * 16, hipMemcpyDeviceToHost, ctx->stream));
+            auto t0 = Clock::now();
+            solved = r.solve != nullptr;
+            if (solved) {
+                const SolveItem sv = solve_item(r, NP);
+                device_grad(r, pb, const_cast<double *>(sv.grad), st);
+                launch_shifted_solve(sv, tikhonov, dt, st);
+                // x, grad and the status word lie one after another
+                HIPCHECK(hipMemcpyAsync(xg.data(), sv.x, (size_t)NP * 16 + 4, hipMemcpyDeviceToHost, st));
+            } else if (P) {
+                HIPCHECK(hipMemcpyAsync(graw.data(), r.graw, (size_t)P * 16, hipMemcpyDeviceToHost, st));
             }
-            HIPCHECK(hipMemcpyAsync(e.data(), r.eraw, 16, hipMemcpyDeviceToHost, ctx->stream));
-            HIPCHECK(hipStreamSynchronize(ctx->stream));
+            if (NP && (G_out || !solved)) {
+                G.resize(2 * (size_t)NP * NP);
+                HIPCHECK(hipMemcpyAsync(G.data(), r.G, (size_t)NP * NP * 16, hipMemcpyDeviceToHost, st));
+            }
+            HIPCHECK(hipMemcpyAsync(e.data(), r.eraw, 16, hipMemcpyDeviceToHost, st));
+            HIPCHECK(hipStreamSynchronize(st));
+            ctx->stats.solve_ms = ms_since(t0);
         });
-        host_unpack_grad(graw, pb, grad.data());
-        auto t0 = Clock::now();
-        std::vector<double> b(NP + 1);
-        for (int i = 0; i < NP; ++i) b[i] = -dt * grad[i];
-        std::vector<double> x(NP + 1);
-        if (NP) qng::solve_shifted(NP, G.data(), tikhonov, b.data(), x.data());
-        ctx->stats.solve_ms = ms_since(t0);
+        if (solved) {
+            int32_t status = 0;
+            std::memcpy(&status, xg.data() + 2 * (size_t)NP, 4);
+            if (status != 0) fail(QNG_E_NOT_SPD, "Re G + eps I is not positive definite (device solve)");
+            std::memcpy(x.data(), xg.data(), (size_t)NP * 8);
+            std::memcpy(grad.data(), xg.data() + NP, (size_t)NP * 8);
+        } else {
+            host_unpack_grad(graw, pb, grad.data());
+            auto t0 = Clock::now();
+            std::vector<double> b(NP + 1);
+            for (int i = 0; i < NP; ++i) b[i] = -dt * grad[i];
+            if (NP) qng::solve_shifted(NP, G.data(), tikhonov, b.data(), x.data());
+            ctx->stats.solve_ms = ms_since(t0);
+        }
         if (NP) std::memcpy(dtheta_out, x.data(), (size_t)NP * 8);
         if (G_out && NP) std::memcpy(G_out, G.data(), (size_t)NP * NP * 16);
         if (grad_out && NP) std::memcpy(grad_out, grad.data(), (size_t)NP * 8);
@@ -1658,7 +1725,9 @@ qng_status qng_step_batched(qng_ctx *ctx, int32_t B, const qng_circuit *circs, c
             apply_metric_settings(ctx, pbs.back());
         }
         std::vector<std::vector<double>> G(B), graw(B);
-        std::vector<double> E(2 * (size_t)B);
+        std::vector<double> E(2 * (size_t)B), xg;
+        std::vector<size_t> xg_off;
+        bool solved = false;
         dispatch(prec, [&](auto tag) {
             using R = decltype(tag);
             const BatchTuning tun = batch_tuning<R>(ctx, pbs, in_states);
@@ -1692,13 +1761,47 @@ qng_status qng_step_batched(qng_ctx *ctx, int32_t B, const qng_circuit *circs, c
                 }
                 e.finish_energy_grad(batch_final_pos(pb.circ), true, nullptr);
             }
+            solved = L.device_solve;
+            if (solved) {
+                std::vector<SolveItem> items(B);
+                int max_np = 0;
+                for (int b = 0; b < B; ++b) {
+                    const int NP = pbs[b].circ.NP;
+                    SolveItem &it = items[b];
+                    it.G = run.G[b];
+                    it.P = NP;
+                    it.A = (double *)(base + L.solve_a[b]);
+                    it.x = (double *)(base + L.xg) + L.xg_off[b];
+                    it.grad = it.x + NP;
+                    it.status = (int32_t *)(it.x + 2 * (size_t)NP);
+                    max_np = std::max(max_np, NP);
+                    CallResult r;
+                    r.graw = (double *)(base + L.graw[b]);
+                    r.param_of = (const int *)(base + L.param_of[b]);
+                    device_grad(r, pbs[b], const_cast<double *>(it.grad), ctx->stream);
+                }
+                if (max_np) {
+                    HIPCHECK(hipMemcpyAsync(base + L.solve_items, items.data(), (size_t)B * sizeof(SolveItem),
+                                            hipMemcpyHostToDevice, ctx->stream));
+                    HIPCHECK(hipStreamSynchronize(ctx->stream));   // `items` is released at the block's end
+                    launch_shifted_solves((const SolveItem *)(base + L.solve_items), B, max_np, tikhonov, dt,
+                                          ctx->stream);
+                }
+                xg.assign(L.xg_doubles, 0.0);
+                xg_off = L.xg_off;
+                HIPCHECK(hipMemcpyAsync(xg.data(), base + L.xg, L.xg_doubles * 8, hipMemcpyDeviceToHost,
+                                        ctx->stream));
+            }
             for (int b = 0; b < B; ++b) {
                 const int P = pbs[b].circ.P, NP = pbs[b].circ.NP;
-                G[b].assign(2 * (size_t)NP * NP + 2, 0.0);
-                graw[b].assign(2 * (size_t)P + 2, 0.0);
-                if (P) {
+                if (!P) continue;
+                if (!solved || (G_out && G_out[b])) {
+                    G[b].resize(2 * (size_t)NP * NP);
                     HIPCHECK(hipMemcpyAsync(G[b].data(), run.G[b], (size_t)NP * NP * 16, hipMemcpyDeviceToHost,
                                             ctx->stream));
+                }
+                if (!solved) {
+                    graw[b].resize(2 * (size_t)P);
                     HIPCHECK(hipMemcpyAsync(graw[b].data(), base + L.graw[b], (size_t)P * 16, hipMemcpyDeviceToHost,
                                             ctx->stream));
                 }
@@ -1714,17 +1817,27 @@ qng_status qng_step_batched(qng_ctx *ctx, int32_t B, const qng_circuit *circs, c
         std::vector<std::vector<double>> grads(B), xs(B);
         for (int b = 0; b < B; ++b) {
             const int NP = pbs[b].circ.NP;
-            std::vector<double> rhs(NP + 1);
             grads[b].assign(NP + 1, 0.0);
             xs[b].assign(NP + 1, 0.0);
+            if (!NP) continue;
+            if (solved) {
+                const double *v = xg.data() + xg_off[b];
+                int32_t status = 0;
+                std::memcpy(&status, v + 2 * (size_t)NP, 4);
+                if (status != 0)
+                    fail(QNG_E_NOT_SPD, "ansatz " + std::to_string(b) +
+                                            ": Re G + eps I is not positive definite (device solve)");
+                std::memcpy(xs[b].data(), v, (size_t)NP * 8);
+                std::memcpy(grads[b].data(), v + NP, (size_t)NP * 8);
+                continue;
+            }
+            std::vector<double> rhs(NP + 1);
             host_unpack_grad(graw[b], pbs[b], grads[b].data());
             for (int i = 0; i < NP; ++i) rhs[i] = -dt * grads[b][i];
-            if (NP) {
-                try {
-                    qng::solve_shifted(NP, G[b].data(), tikhonov, rhs.data(), xs[b].data());
-                } catch (const Error &e) {
-                    fail(e.status, "ansatz " + std::to_string(b) + ": " + e.msg);
-                }
+            try {
+                qng::solve_shifted(NP, G[b].data(), tikhonov, rhs.data(), xs[b].data());
+            } catch (const Error &e) {
+                fail(e.status, "ansatz " + std::to_string(b) + ": " + e.msg);
             }
         }
         for (int b = 0; b < B; ++b) {
@@ -1871,12 +1984,11 @@ qng_status qng_step_dev(qng_ctx *ctx, const qng_circuit *circ, const void *in_st
             // products keep their real parts
             spec.real_products = G_dev == nullptr;
             CallResult r = run<R>(ctx, pb, spec);
-            // solve workspace: A (NP*NP), y, x, grad (NP each), status
-            double *A = (double *)r.solve;
-            double *y = A + (size_t)NP * NP, *x = y + NP, *grad = x + NP;
-            int32_t *status = (int32_t *)(grad + NP);
+            const SolveItem sv = solve_item(r, NP);
+            double *x = sv.x, *grad = const_cast<double *>(sv.grad);
+            int32_t *status = sv.status;
             device_grad(r, pb, grad, st);
-            if (NP) launch_shifted_solve(r.G, NP, tikhonov, grad, dt, A, y, x, status, st);
+            if (NP) launch_shifted_solve(sv, tikhonov, dt, st);
             else HIPCHECK(hipMemsetAsync(status, 0, sizeof(int32_t), st));
             // every output follows the solve's status: nothing is written when
             // Re G + eps I is not positive definite

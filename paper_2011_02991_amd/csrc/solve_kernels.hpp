@@ -1,21 +1,34 @@
-// solve_kernels.hpp -- device launchers of the step's shifted solve (Sec. 1:
-// (Re G + eps I) dtheta = -dt grad E).  All pointers are device pointers;
-// launches are asynchronous on `st`.
+// solve_kernels.hpp -- the natural-gradient step's shifted solve on the device.
 #pragma once
 
 #include <hip/hip_runtime_api.h>
 
+#include <cstddef>
 #include <cstdint>
 
 namespace qng {
 
-// x solves (Re G + eps I) x = -dt grad by Cholesky in FP64 (one work-group).
-// G: P x P complex row-major; grad, x: P doubles; A: P*P doubles and y: P
-// doubles of scratch.  *status <- 0, or QNG_E_NOT_SPD (-7) with x untouched.
-void launch_shifted_solve(const double *G, int P, double eps, const double *grad, double dt, double *A, double *y,
-                          double *x, int32_t *status, hipStream_t st);
+// One shifted system (Re G + eps I) x = -dt grad, all in device memory.  G:
+// P x P complex row-major (its real part is used); grad: P doubles; A: scratch
+// of (P + 1) P doubles (the lower triangle and, as row P, the right-hand side);
+// x: P doubles; status: 0, or -7 (QNG_E_NOT_SPD) when the matrix is not
+// positive definite (x is then not meaningful).
+struct SolveItem {
+    const double *G;
+    const double *grad;
+    double *A;
+    double *x;
+    int32_t *status;
+    int32_t P;
+    int32_t pad;
+};
 
-// dst[0 .. count) <- src[0 .. count) if *status == 0, else nothing.
+// Solves one system, or `n` systems listed in device memory (max_P: the
+// largest of them) together.  Bitwise reproducible.
+void launch_shifted_solve(const SolveItem &one, double eps, double dt, hipStream_t st);
+void launch_shifted_solves(const SolveItem *items_dev, int n, int max_P, double eps, double dt, hipStream_t st);
+
+// dst[0 .. count) <- src when *status is 0 (device words).
 void launch_copy_if_ok(const int32_t *status, const double *src, double *dst, int64_t count, hipStream_t st);
 
 }  // namespace qng
