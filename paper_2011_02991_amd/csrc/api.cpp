@@ -1118,15 +1118,7 @@ BatchRun batch_metric(qng_ctx *ctx, const std::vector<Problem> &pbs, const doubl
                 double *o = &fm[(size_t)(S.gate_base[i] + r.pos) * 8];
                 o[0] = m.a.real(); o[1] = m.a.imag(); o[2] = m.b.real(); o[3] = m.b.imag();
                 o[4] = m.c.real(); o[5] = m.c.imag(); o[6] = m.d.real(); o[7] = m.d.imag();
-                const Shear sh = adjoint_shear(r.axis, pb.adj[r.pos]);
-                am[(size_t)(S.gate_base[i] + r.pos) * 8 + 0] = sh.u;
-                am[(size_t)(S.gate_base[i] + r.pos) * 8 + 1] = sh.w;
-                if (r.ctrl >= 0) {
-                    // controlled rotations: the adjoint as a plane rotation
-                    const PlaneRot pl = adjoint_plane(r.axis, pb.adj[r.pos]);
-                    am[(size_t)(S.gate_base[i] + r.pos) * 8 + 2] = pl.c;
-                    am[(size_t)(S.gate_base[i] + r.pos) * 8 + 3] = pl.s;
-                }
+                adjoint_row(r.axis, r.ctrl >= 0, pb.adj[r.pos], &am[(size_t)(S.gate_base[i] + r.pos) * 8]);
             }
             // the fixed rotations of rewritten Pauli strings: the forward
             // matrix and the adjoint's shear, as for the parameterised ones
@@ -1137,9 +1129,8 @@ BatchRun batch_metric(qng_ctx *ctx, const std::vector<Problem> &pbs, const doubl
                 double *o = &fm[(size_t)(S.gate_base[i] + pos) * 8];
                 o[0] = m.a.real(); o[1] = m.a.imag(); o[2] = m.b.real(); o[3] = m.b.imag();
                 o[4] = m.c.real(); o[5] = m.c.imag(); o[6] = m.d.real(); o[7] = m.d.imag();
-                const Shear sh = adjoint_shear(kind == QNG_RX ? AX_X : kind == QNG_RY ? AX_Y : AX_Z, pb.adj[pos]);
-                am[(size_t)(S.gate_base[i] + pos) * 8 + 0] = sh.u;
-                am[(size_t)(S.gate_base[i] + pos) * 8 + 1] = sh.w;
+                adjoint_row(kind == QNG_RX ? AX_X : kind == QNG_RY ? AX_Y : AX_Z, false, pb.adj[pos],
+                            &am[(size_t)(S.gate_base[i] + pos) * 8]);
             }
         }
         std::vector<float> am32(am.begin(), am.end());

@@ -78,7 +78,7 @@ BatchSchedule build_batch_schedule(const std::vector<const Circuit *> &members,
             S.passes.push_back(dp);
         }
         for (DevOp op : p.dev_ops) {
-            if (op.type == OPC_XPOSE) op.aux += (int32_t)map_base;
+            if (op.type == OPC_XPOSE || op.type == OPC_CZS) op.aux += (int32_t)map_base;
             if (op.gate >= 0) op.gate += (int32_t)S.gate_base[b];
             S.ops.push_back(op);
         }

@@ -228,6 +228,17 @@ PlaneRot adjoint_plane(int axis, const Mat2 &adj) {
     return PlaneRot{adj.a.real(), s};
 }
 
+void adjoint_row(int axis, bool controlled, const Mat2 &adj, double *row) {
+    const Shear sh = adjoint_shear(axis, adj);
+    row[0] = sh.u;
+    row[1] = sh.w;
+    if (controlled) {
+        const PlaneRot pl = adjoint_plane(axis, adj);
+        row[2] = pl.c;
+        row[3] = pl.s;
+    }
+}
+
 std::vector<PauliTerm> compile_hamiltonian(const qng_circuit *c, const qng_pauli_sum *h) {
     std::vector<PauliTerm> out(h->n_terms);
     for (int t = 0; t < h->n_terms; ++t) {

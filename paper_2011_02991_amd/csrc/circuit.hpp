@@ -108,6 +108,9 @@ struct PlaneRot {
     double c, s;
 };
 PlaneRot adjoint_plane(int axis, const Mat2 &adj);
+// A gate's row (8 values) of the sweep kernels' table: the shear (u, w), then for
+// a controlled rotation its plane rotation (c, s).
+void adjoint_row(int axis, bool controlled, const Mat2 &adj, double *row);
 
 // Pauli string in bit-mask form: (sigma psi)[x] = (-i)^{nY} (-1)^{popcount(x & zy)} psi[x ^ flip],
 // with flip = positions of X and Y letters, zy = positions of Z and Y letters

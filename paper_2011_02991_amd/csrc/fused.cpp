@@ -31,9 +31,7 @@ void fill_fixed_shears(const Circuit &c, const std::vector<Mat2> &adj, std::vect
     for (int pos = 0; pos < c.M; ++pos) {
         if (!c.is_fixed_rotation(pos)) continue;
         const int kind = c.gates[pos].kind;
-        const Shear sh = adjoint_shear(kind == QNG_RX ? AX_X : kind == QNG_RY ? AX_Y : AX_Z, adj[pos]);
-        mats[(size_t)pos * 8 + 0] = sh.u;
-        mats[(size_t)pos * 8 + 1] = sh.w;
+        adjoint_row(kind == QNG_RX ? AX_X : kind == QNG_RY ? AX_Y : AX_Z, false, adj[pos], &mats[(size_t)pos * 8]);
     }
 }
 
@@ -167,14 +165,7 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
         double *d = &fmats[(size_t)r.pos * 8];
         d[0] = m.a.real(); d[1] = m.a.imag(); d[2] = m.b.real(); d[3] = m.b.imag();
         d[4] = m.c.real(); d[5] = m.c.imag(); d[6] = m.d.real(); d[7] = m.d.imag();
-        const Shear sh = adjoint_shear(r.axis, adj[r.pos]);
-        mats[(size_t)r.pos * 8 + 0] = sh.u;
-        mats[(size_t)r.pos * 8 + 1] = sh.w;
-        if (r.ctrl >= 0) {
-            const PlaneRot pl = adjoint_plane(r.axis, adj[r.pos]);
-            mats[(size_t)r.pos * 8 + 2] = pl.c;
-            mats[(size_t)r.pos * 8 + 3] = pl.s;
-        }
+        adjoint_row(r.axis, r.ctrl >= 0, adj[r.pos], &mats[(size_t)r.pos * 8]);
     }
     fill_fixed_shears(c, adj, mats);
     std::vector<float> mats32(mats.begin(), mats.end());
@@ -219,9 +210,7 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
             const int kind = c.gates[pos].kind;
             if (kind > QNG_RZ) continue;
             const int axis = kind == QNG_RX ? AX_X : kind == QNG_RY ? AX_Y : AX_Z;
-            const Shear sh = adjoint_shear(axis, fwd[pos]);
-            fshear[(size_t)pos * 8 + 0] = sh.u;
-            fshear[(size_t)pos * 8 + 1] = sh.w;
+            adjoint_row(axis, false, fwd[pos], &fshear[(size_t)pos * 8]);
             neg[pos] = fwd[pos].a.real() < 0;
         }
         int from = c.rots[0].pos;
@@ -661,17 +650,12 @@ bool run_fused_apply(const SweepPlan &a, const Circuit &c, const std::vector<Mat
     for (int pos = from; pos < c.M; ++pos) {
         const int kind = c.gates[pos].kind;
         if (kind == QNG_CNOT || kind == QNG_CZ) continue;
-        R *o = &mats[(size_t)pos * 8];
-        if (kind <= QNG_RZ) {
-            const Shear sh = adjoint_shear(kind == QNG_RX ? AX_X : kind == QNG_RY ? AX_Y : AX_Z, fwd[pos]);
-            o[0] = (R)sh.u;
-            o[1] = (R)sh.w;
-            negated ^= fwd[pos].a.real() < 0;
-        } else {
-            const PlaneRot pl = adjoint_plane(kind == QNG_CRX ? AX_X : kind == QNG_CRY ? AX_Y : AX_Z, fwd[pos]);
-            o[2] = (R)pl.c;
-            o[3] = (R)pl.s;
-        }
+        const bool controlled = kind > QNG_RZ;
+        const int axis = kind == QNG_RX || kind == QNG_CRX ? AX_X : kind == QNG_RY || kind == QNG_CRY ? AX_Y : AX_Z;
+        double row[4] = {0, 0, 0, 0};
+        adjoint_row(axis, controlled, fwd[pos], row);
+        for (int k = 0; k < 4; ++k) mats[(size_t)pos * 8 + k] = (R)row[k];
+        if (!controlled) negated ^= fwd[pos].a.real() < 0;
     }
     std::vector<LaunchItem> items;
     for (size_t t = 0; t < a.dev_passes.size(); ++t) {
@@ -749,14 +733,7 @@ void run_fused_gradient(const SweepPlan &g, const Circuit &c, const std::vector<
     task_begin.push_back((uint32_t)tasks.size());
     std::vector<double> mats((size_t)c.M * 8, 0.0);
     for (const Rot &r : c.rots) {
-        const Shear sh = adjoint_shear(r.axis, adj[r.pos]);
-        mats[(size_t)r.pos * 8 + 0] = sh.u;
-        mats[(size_t)r.pos * 8 + 1] = sh.w;
-        if (r.ctrl >= 0) {
-            const PlaneRot pl = adjoint_plane(r.axis, adj[r.pos]);
-            mats[(size_t)r.pos * 8 + 2] = pl.c;
-            mats[(size_t)r.pos * 8 + 3] = pl.s;
-        }
+        adjoint_row(r.axis, r.ctrl >= 0, adj[r.pos], &mats[(size_t)r.pos * 8]);
     }
     fill_fixed_shears(c, adj, mats);
     std::vector<float> mats32(mats.begin(), mats.end());

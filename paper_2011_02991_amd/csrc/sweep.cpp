@@ -327,6 +327,44 @@ uint8_t location(const DevMap &mp, int rb, int m, int localbit) {
     return kLocBase;
 }
 
+bool is_cz(const Event &e) { return e.kind == EV_UNAPPLY && e.gkind == QNG_CZ; }
+
+// A phase's events in the order they run, with the ranges of CZs that run as
+// one.  CZs wait until nothing else of the phase can go, so that as many as
+// possible meet; those that are ready are then one sign per amplitude.
+struct PhaseOrder {
+    std::vector<int> order;
+    std::vector<std::pair<int, int>> cz_sets;   // ranges of `order`, two CZs or more each
+};
+
+PhaseOrder order_phase(const std::vector<Event> &ev, const std::vector<int> &phase, int n) {
+    PhaseOrder po;
+    std::vector<int> pending = phase, keep;
+    while (!pending.empty()) {
+        // the ready events that are no CZs; when there are none, the ready CZs
+        for (int round = 0; round < 2; ++round) {
+            Blockers bl(n);
+            keep.clear();
+            const size_t begin = po.order.size();
+            for (int idx : pending) {
+                const Event &e = ev[idx];
+                if (is_cz(e) == (round == 1) && bl.ready(e) && (round == 0 || po.order.size() - begin < kMaxCzSet)) {
+                    po.order.push_back(idx);
+                } else {
+                    bl.block(e);
+                    keep.push_back(idx);
+                }
+            }
+            if (po.order.size() == begin) continue;
+            if (round == 1 && po.order.size() - begin > 1) po.cz_sets.push_back({(int)begin, (int)po.order.size()});
+            break;
+        }
+        if (keep.size() == pending.size()) fail(QNG_E_DEVICE, "sweep planner: no event of a phase is ready (internal error)");
+        pending.swap(keep);
+    }
+    return po;
+}
+
 // Destinations of a block's inner products: element (r, column of phi register
 // b) -> r * stride + col0 + b (metric: r * P + s_b; gradient: r); the T product
 // of a seeded column s_b -> t_base + s_b.
@@ -417,10 +455,14 @@ HostPass make_pass(const Circuit &c, const SlotDest &sd, const std::vector<Event
     for (size_t ph = 0; ph < phases.size(); ++ph) {
         if (ph > 0 || load_xpose) xpose_to(phases[ph].first);
         const DevMap &mp = hp.maps[cur_map];
-        const std::vector<int> &order = phases[ph].second;
+        const PhaseOrder po = order_phase(ev, phases[ph].second, c.n);
+        const std::vector<int> &order = po.order;
+        size_t next_set = 0;
+        int set_begin = 0;
         auto loc_of_qubit = [&](int q) -> uint8_t { return local[q] < 0 ? kLocBase : location(mp, rb, m, local[q]); };
         for (size_t k = 0; k < order.size(); ++k) {
             const Event &e = ev[order[k]];
+            if (next_set < po.cz_sets.size() && (int)k == po.cz_sets[next_set].first) set_begin = (int)hp.ops.size();
             DevOp op{};
             op.b0 = op.b1 = kLocBase;
             op.gate = -1;
@@ -498,6 +540,10 @@ HostPass make_pass(const Circuit &c, const SlotDest &sd, const std::vector<Event
                 }
             }
             hp.ops.push_back(op);
+            if (next_set < po.cz_sets.size() && (int)k + 1 == po.cz_sets[next_set].second) {
+                hp.cz_sets.push_back({set_begin, (int)hp.ops.size()});
+                ++next_set;
+            }
         }
     }
     // store with the carriers on the lanes
@@ -564,7 +610,6 @@ void flatten(SweepPlan &plan, const Circuit &c) {
             DevPass dp{};
             const uint32_t map_base = (uint32_t)plan.dev_maps.size();
             dp.op_begin = (uint32_t)plan.dev_ops.size();
-            dp.n_ops = (uint32_t)hp.ops.size();
             dp.n_slots = (uint16_t)hp.slot_dest.size();
             dp.m = (uint8_t)hp.tile.size();
             dp.n = (uint8_t)c.n;
@@ -578,11 +623,34 @@ void flatten(SweepPlan &plan, const Circuit &c) {
                 if (!in[q]) dp.rest_q[k++] = (uint8_t)q;
             dp.nrest = (uint8_t)k;
             bool has_cnot = false;
-            for (DevOp op : hp.ops) {
-                if (op.type == OP_ZSUM) dp.has_zsum = 1;
-                if (op.type == OP_CNOT) has_cnot = true;
-                if (op.type == OP_XPOSE) op.aux += (int32_t)map_base;
-                op.type = device_opcode(op);
+            std::vector<CzSet> sets;
+            dp.n_ops = 0;
+            size_t next_set = 0;
+            for (size_t k = 0; k < hp.ops.size(); ++k) {
+                DevOp op = hp.ops[k];
+                if (next_set < hp.cz_sets.size() && (int)k == hp.cz_sets[next_set].first) {
+                    const size_t end = (size_t)hp.cz_sets[next_set++].second;
+                    CzSet set{};
+                    op = DevOp{};
+                    for (; k < end; ++k) {
+                        const DevOp &o = hp.ops[k];
+                        if (o.type != OP_CZ || op.n_cz >= (uint32_t)kMaxCzSet)
+                            fail(QNG_E_DEVICE, "device op: not a set of CZs (internal)");
+                        set.cz[op.n_cz++] = (uint32_t)o.b0 | ((uint32_t)o.q0 << 8) | ((uint32_t)o.b1 << 16) |
+                                            ((uint32_t)o.q1 << 24);
+                    }
+                    --k;
+                    op.type = OPC_CZS;
+                    op.b0 = op.b1 = kLocBase;
+                    op.gate = -1;
+                    op.aux = (int32_t)(map_base + hp.maps.size() + sets.size() * kCzSetMaps);
+                    sets.push_back(set);
+                } else {
+                    if (op.type == OP_ZSUM) dp.has_zsum = 1;
+                    if (op.type == OP_CNOT) has_cnot = true;
+                    if (op.type == OP_XPOSE) op.aux += (int32_t)map_base;
+                    op.type = device_opcode(op);
+                }
                 const int h2 = device_handler2(op.type);
                 if (h2 >= 0) {
                     op.hlo = op.hhi = 0;
@@ -595,8 +663,14 @@ void flatten(SweepPlan &plan, const Circuit &c) {
                     op.h2 = 0;
                 }
                 plan.dev_ops.push_back(op);
+                ++dp.n_ops;
             }
             for (const DevMap &mp : hp.maps) plan.dev_maps.push_back(mp);
+            for (const CzSet &set : sets) {
+                const size_t at = plan.dev_maps.size();
+                plan.dev_maps.resize(at + kCzSetMaps);
+                std::memcpy((void *)&plan.dev_maps[at], &set, sizeof set);
+            }
             plan.dev_passes.push_back(dp);
             plan.max_slots = std::max<int64_t>(plan.max_slots, dp.n_slots);
             plan.transposes += hp.transposes;
@@ -760,13 +834,14 @@ int device_handler(uint8_t c) {
     if (c == OPC_ZSUM) return HB_ZSUM;
     if (c == OPC_XPOSE) return HB_XPOSE;
     if (c == OPC_SEED) return HB_SEED;
+    if (c == OPC_CZS) return HB_CZ;
     fail(QNG_E_DEVICE, "device handler: unknown op code (internal)");
     return 0;
 }
 
 int device_handler2(uint8_t c) {
     // the controlled-rotation codes map onto the second word in order
-    if (c < OPC_CROT_X) return -1;
+    if (c < OPC_CROT_X || c == OPC_CZS) return -1;
     if (c > OPC_CSEED) fail(QNG_E_DEVICE, "device handler: unknown op code (internal)");
     static_assert(OPC_CSEED - OPC_CROT_X == HB2_CSEED && OPC_PRODC_Y - OPC_CROT_X == HB2_PRODC_Y &&
                       OPC_CDIAG - OPC_CROT_X == HB2_CDIAG,

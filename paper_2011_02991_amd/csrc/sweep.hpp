@@ -105,7 +105,8 @@ enum : uint8_t {
     OPC_CDIAG = 100,
     OPC_PRODCDIAG = 101,
     OPC_PRODCZ = 102,
-    OPC_CSEED = 103
+    OPC_CSEED = 103,
+    OPC_CZS = 104             // the signs of several CZs (CzSet)
 };
 
 // Location of a local bit in the current thread mapping: a register position
@@ -128,7 +129,7 @@ struct DevOp {  // 32 bytes
                       // OP_SEED: the phi register seeded
     uint32_t hlo, hhi;   // device images: one-hot handler bit (HB_* below), low and high word
     uint32_t h2;         // device images: one-hot bit of the controlled-rotation handlers (HB2_*), or 0
-    uint32_t pad1;
+    uint32_t n_cz;       // device images, OPC_CZS: number of CZs
 };
 
 struct DevPass {  // 64 bytes, read through a pointer with scalar loads
@@ -199,8 +200,18 @@ int device_handler2(uint8_t opcode);
 static_assert(sizeof(DevOp) == 32, "DevOp layout");
 static_assert(sizeof(DevMap) == 16, "DevMap layout");
 
+// Several CZs that run as one op (OPC_CZS).  The op's aux names the set's first
+// entry in the table of thread mappings, where it fills kCzSetMaps entries.
+constexpr int kMaxCzSet = 24;
+struct CzSet {
+    uint32_t cz[kMaxCzSet];   // locations and qubits of a CZ's two bits: b0, q0 << 8, b1 << 16, q1 << 24
+};
+constexpr int kCzSetMaps = (int)(sizeof(CzSet) / sizeof(DevMap));
+static_assert(sizeof(CzSet) % sizeof(DevMap) == 0, "CzSet fills whole DevMap entries");
+
 struct HostPass {
     std::vector<uint8_t> tile;          // local bit -> qubit
+    std::vector<std::pair<int, int>> cz_sets;   // ranges [begin, end) of ops: CZs that run as one
     std::vector<DevOp> ops;             // includes OP_XPOSE (aux = index into maps)
     std::vector<int32_t> slot_dest;     // per slot: (rotation r) * P + column s
     std::vector<DevMap> maps;           // thread mappings of this pass

@@ -98,15 +98,14 @@ __device__ __forceinline__ void row_sum(double &a, double &b) {
     b += dpp_shifted<0x118>(b);
 }
 
-// LDS layout of the sweep kernel: the exchange buffer [2^m] (at least the
-// kMaxBlockWidth x kWaves tile sums <lambda|phi_b>, which use its start while
-// no exchange runs: both sit between barriers), one sink entry per thread,
-// the per-wavefront partials of the inner products [kMaxSlots][kWaves].
-constexpr int kLdsTailEntries = kThreads + kMaxSlots * kWaves;
+// LDS layout of the sweep kernel: the exchange buffer [2^m], one sink entry per
+// lane of two wavefronts, the tile sums of the phi registers [kMaxBlockWidth]
+// [kWaves], the per-wavefront partials of the inner products [kMaxSlots][kWaves].
+constexpr int kSinks = 128;
+constexpr int kTileSums = kMaxBlockWidth * kWaves;
+constexpr int kLdsTailEntries = kSinks + kTileSums + kMaxSlots * kWaves;
 template <typename CX> __host__ __device__ constexpr size_t xbuf_bytes(int m) {
-    return ((size_t)1 << m) * sizeof(CX) > (size_t)kMaxBlockWidth * kWaves * 16
-               ? ((size_t)1 << m) * sizeof(CX)
-               : (size_t)kMaxBlockWidth * kWaves * 16;
+    return ((size_t)1 << m) * sizeof(CX) > 256 ? ((size_t)1 << m) * sizeof(CX) : 256;
 }
 
 // Store a per-lane partial of slot `slot` of `dst`: one value per wavefront.
@@ -727,6 +726,7 @@ struct OpD {
     int32_t gate, aux;
     uint64_t hf;   // one-hot handler bit (sweep.hpp, HB_*)
     uint32_t h2;   // one-hot bit of the second word (HB2_*), or 0
+    uint32_t n_cz; // OPC_CZS: number of CZs
     __device__ __forceinline__ int type() const { return (int)(w0 & 0xffu); }
     __device__ __forceinline__ uint8_t b0() const { return (uint8_t)((w0 >> 8) & 0xffu); }
     __device__ __forceinline__ uint8_t b1() const { return (uint8_t)((w0 >> 16) & 0xffu); }
@@ -738,7 +738,7 @@ struct OpD {
 __device__ __forceinline__ OpD load_op(const DevOp *p) {
     const uint4 v = *reinterpret_cast<const uint4 *>(p);
     const uint4 h = *(reinterpret_cast<const uint4 *>(p) + 1);
-    return OpD{v.x, v.y, (int32_t)v.z, (int32_t)v.w, (uint64_t)h.x | ((uint64_t)h.y << 32), h.z};
+    return OpD{v.x, v.y, (int32_t)v.z, (int32_t)v.w, (uint64_t)h.x | ((uint64_t)h.y << 32), h.z, h.w};
 }
 
 constexpr uint64_t hbit(int b) { return uint64_t(1) << b; }
@@ -1099,6 +1099,59 @@ __device__ __forceinline__ void crot_handlers(Regs<CT, T, W> &x, uint32_t h2, ui
     }
 }
 
+// ------------------------------------------------------- sets of CZs
+//
+// The CZs of a phase that are ready together (CzSet, sweep.hpp) are one sign per
+// amplitude: 104 vector instructions (four phi registers of 8 amplitudes) and
+// about 15 per CZ instead of 104 each.  A step of 20 qubits, 400 parameters
+// (RX, RY, CZ ring, complex128) has 21.6 CZs in a pass, in 8.0 sets:
+// 47.4 -> 46.3 ms.
+//
+// What a handler may not do is wait for memory: with three wavefronts per SIMD a
+// load or a spilled register inside the op loop costs more than the instructions
+// a larger set saves.  (All Z products and RZs of a phase as one op, from one
+// pointwise product and a Walsh transform over the lanes: 16 % fewer vector
+// instructions, twice the wait cycles, up to 30 % slower; a phase has only two to
+// four of them.)
+
+// a scalar that is in its register from here on
+template <typename V> __device__ __forceinline__ void arrived(V &v) { asm volatile("" : "+s"(v)); }
+
+// Mask over the thread's amplitudes of the sign of n CZs, read four at a time
+// (one wait for four; what is past the last one is left out).
+template <int T>
+__device__ __forceinline__ uint32_t cz_signs(const uint32_t *__restrict__ cz, uint32_t n, int tid, uint64_t base) {
+    uint32_t neg = 0;
+    for (uint32_t k = 0; k < n; k += 4) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(cz + k);
+        uint32_t c[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) arrived(c[i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (k + i >= n) break;
+            neg ^= loc_mask<T>((uint8_t)c[i], (uint8_t)(c[i] >> 8), tid, base) &
+                   loc_mask<T>((uint8_t)(c[i] >> 16), (uint8_t)(c[i] >> 24), tid, base);
+        }
+    }
+    return neg;
+}
+
+template <int T, typename CT, int W>
+__device__ __forceinline__ void apply_signs(Regs<CT, T, W> &x, uint32_t neg) {
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+        const CT sg = sel<CT>((neg >> i) & 1u, (CT)-1, (CT)1);
+        x.ar[i] *= sg;
+        x.ai[i] *= sg;
+#pragma unroll
+        for (int b = 0; b < W; ++b) {
+            x.br[b][i] *= sg;
+            x.bi[b][i] *= sg;
+        }
+    }
+}
+
 // One register of the tile through the exchange buffer, from mapping `from`
 // to mapping `to`.  With RECOMPUTE the slots are recomputed for every
 // register from an opaque copy of the thread index (the kernels with two phi
@@ -1160,39 +1213,41 @@ __device__ __forceinline__ void store_reg(void *g, const uint64_t (&off)[T], con
     }
 }
 
-// Tile sums <lambda|phi_b>_tile of phi registers B0 .. B1-1, summed over the
-// work-group (uniform control flow: contains barriers).
-template <int T, typename CT, int W, int B0, int B1, int N>
-__device__ __forceinline__ void tile_sums(const Regs<CT, T, W> &x, double2 *sink, double2 *zs, int tid,
-                                          double (&Sr)[N], double (&Si)[N]) {
-    __syncthreads();   // earlier readers of zs are done
+// Tile sums <lambda|phi_b>_tile for the Z products outside the tile (OP_ZSUM),
+// each wavefront its part: with one phi register in registers (the sum is in lane
+// 15), with more in LDS in front of `red` (slot kTileSumSlot + b), where they spare
+// 4 W registers through the whole op loop (four phi registers, real products:
+// spilled bytes 40 -> 24; one phi register has them to spare, and saves the wait).
+constexpr int kTileSumSlot = -kMaxBlockWidth;
+template <int W> struct TileSums {
+    static constexpr bool kInLds = W > 1;
+    double r[W > 0 && !kInLds ? W : 1], i[W > 0 && !kInLds ? W : 1];
+};
+// those of phi registers B0 .. B1-1
+template <int T, typename CT, int W, int B0, int B1>
+__device__ __forceinline__ void tile_sums(const Regs<CT, T, W> &x, TileSums<W> &ts, double2 *sink, double2 *red,
+                                          int tid) {
 #pragma unroll
     for (int b = B0; b < B1; ++b) {
         double sr, si;
         prod_plain<T, CT>(x.ar, x.ai, x.br[b], x.bi[b], sr, si);
-        row_store(sink, zs, b, tid, sr, si);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int b = B0; b < B1; ++b) {
-        double ar = 0.0, ai = 0.0;
-        for (int w = 0; w < kWaves; ++w) {
-            ar += zs[b * kWaves + w].x;
-            ai += zs[b * kWaves + w].y;
+        if constexpr (TileSums<W>::kInLds) {
+            row_store(sink, red, kTileSumSlot + b, tid, sr, si);
+        } else {
+            row_sum(sr, si);
+            ts.r[b] = across_rows(sr);
+            ts.i[b] = across_rows(si);
         }
-        Sr[b] = ar;
-        Si[b] = ai;
     }
-    __syncthreads();   // zs lies in the exchange buffer: read before the next exchange
+    if constexpr (TileSums<W>::kInLds) __builtin_amdgcn_wave_barrier();
 }
 
 // Seed of a lower column of a block: phi register SB <- sigma lambda when the
 // op names register SB, then <lambda|phi> into the op's slot and the pass's
-// tile sums of that register (uniform control flow: contains barriers).
+// tile sums of that register.
 template <int SB, int RB, int T, typename CT, int W>
 __device__ __forceinline__ void seed_handler(Regs<CT, T, W> &x, const OpD &op, int tid, uint64_t base,
-                                             double2 *sink, double2 *red, double2 *zs, bool pass_zsum,
-                                             double (&Sr)[W], double (&Si)[W]) {
+                                             double2 *sink, double2 *red, bool pass_zsum, TileSums<W> &ts) {
     if constexpr (SB + 1 < W) {
         if (op.aux == SB) {
             seed_phi<SB, RB, T, CT, W>(x, op.w0 >> 24, op.b0(), op.q0(), tid, base);
@@ -1200,7 +1255,7 @@ __device__ __forceinline__ void seed_handler(Regs<CT, T, W> &x, const OpD &op, i
                 double pr, pi;
                 prod_plain<T, CT>(x.ar, x.ai, x.br[SB], x.bi[SB], pr, pi);
                 row_store(sink, red, op.slot(), tid, pr, pi);
-                if (pass_zsum) tile_sums<T, CT, W, SB, SB + 1>(x, sink, zs, tid, Sr, Si);
+                if (pass_zsum) tile_sums<T, CT, W, SB, SB + 1>(x, ts, sink, red, tid);
             }
         }
     }
@@ -1250,9 +1305,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
     using CX = typename Amp<CT>::T;
     CX *xbuf = (CX *)smem;                                // [2^m] exchange buffer
     double2 *tail = (double2 *)(smem + xbuf_bytes<CX>(m));
-    double2 *sink = tail + tid;                           // this thread's sink entry
-    double2 *red = tail + kThreads;                       // [kMaxSlots][kWaves]
-    double2 *zs = (double2 *)xbuf;                        // [W][kWaves], inside the exchange buffer
+    double2 *sink = tail + (tid & (kSinks - 1));          // this lane's sink entry
+    double2 *red = tail + kSinks + kTileSums;             // [kMaxSlots][kWaves]
 
     uint64_t base = 0;
     const PassBytes pbytes = load_pass_bytes(pp);
@@ -1285,10 +1339,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
     }
     // plain tile sums <A|B_b>_tile for Z inner products on qubits outside the
     // tile (a phi register seeded in this pass gets its sum at the seed)
-    double Sr[W > 0 ? W : 1], Si[W > 0 ? W : 1];
-#pragma unroll
-    for (int b = 0; b < W; ++b) Sr[b] = Si[b] = 0.0;
-    if (!kNoProducts && pass_zsum) tile_sums<T, CT, W, 0, W>(x, sink, zs, tid, Sr, Si);
+    TileSums<W> ts;
+    ts.r[0] = ts.i[0] = 0.0;
+    if (!kNoProducts && pass_zsum) tile_sums<T, CT, W, 0, W>(x, ts, sink, red, tid);
 
     // ---- operations.  Each op carries a one-hot handler bit; the handlers run
     // under independent tests of that word (by group, register bit, kind),
@@ -1296,15 +1349,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
     const CT *__restrict__ mt = (const CT *)mats;
     const int n_ops = (int)ph0.y;
     const DevOp *op_ptr = ops + ph0.x;
-    // The descriptor of the next op is fetched while the current one runs, and
-    // the current op's shear parameters (unused by ops without a gate) before
-    // the handlers, so scalar-load latency overlaps the work.
-    OpD nxt = load_op(op_ptr);
+    // The descriptor of the op after next and the shear parameters of the next
+    // one (unused by ops without a gate) are fetched while the current one runs,
+    // so that no handler waits for scalar loads at its start (a rotation on its
+    // own is 120 instructions: a wait for its two parameters was a third of it).
+    OpD nxt = load_op(op_ptr), aft = load_op(op_ptr + (n_ops > 1 ? 1 : 0));
+    const CT *nrow = mt + (size_t)(nxt.gate > 0 ? nxt.gate : 0) * 8;
+    CT nu = nrow[0], nw = nrow[1];
     for (int oi = 0; oi < n_ops; ++oi) {
-        const OpD op = nxt;
-        nxt = load_op(op_ptr + (oi + 1 < n_ops ? oi + 1 : oi));
-        const CT *mrow = mt + (size_t)(op.gate > 0 ? op.gate : 0) * 8;
-        const CT u = mrow[0], w = mrow[1];
+        const OpD op = CTRL ? load_op(op_ptr + oi) : nxt;
+        const CT *mrow = CTRL ? mt + (size_t)(op.gate > 0 ? op.gate : 0) * 8 : nrow;
+        const CT u = CTRL ? mrow[0] : nu, w = CTRL ? mrow[1] : nw;
+        nxt = aft;
+        aft = load_op(op_ptr + (oi + 2 < n_ops ? oi + 2 : n_ops - 1));
+        nrow = mt + (size_t)(nxt.gate > 0 ? nxt.gate : 0) * 8;
+        nu = nrow[0];
+        nw = nrow[1];
         const uint64_t hf = op.hf;
         const int fa = (W == 1) ? 0 : op.aux;   // inner products: first active phi register
         // Handlers under independent tests of the handler word, nested by
@@ -1422,7 +1482,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
                             double pr, pi;
                             prod_plain<T, CT>(x.ar, x.ai, x.br[0], x.bi[0], pr, pi);
                             row_store(sink, red, slot, tid, pr, pi);
-                            if (pass_zsum) tile_sums<T, CT, W, 0, 1>(x, sink, zs, tid, Sr, Si);
+                            if (pass_zsum) tile_sums<T, CT, W, 0, 1>(x, ts, sink, red, tid);
                         }
                     }
                 }
@@ -1430,28 +1490,24 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
         }
         if (hf & (hbit(HB_XPOSE) | hbit(HB_CZ) | hbit(HB_ZSUM) | hbit(HB_SEED))) {
             if (hf & hbit(HB_CZ)) {
-                const uint32_t neg = loc_mask<T>(op.b0(), op.q0(), tid, base) & loc_mask<T>(op.b1(), op.q1(), tid, base);
-#pragma unroll
-                for (int i = 0; i < T; ++i) {
-                    const CT sg = sel<CT>((neg >> i) & 1u, (CT)-1, (CT)1);
-                    x.ar[i] *= sg;
-                    x.ai[i] *= sg;
-#pragma unroll
-                    for (int b = 0; b < W; ++b) {
-                        x.br[b][i] *= sg;
-                        x.bi[b][i] *= sg;
-                    }
-                }
+                // one CZ, or a set of them
+                const uint32_t neg = op.n_cz ? cz_signs<T>(reinterpret_cast<const uint32_t *>(maps + op.aux), op.n_cz, tid, base)
+                                           : loc_mask<T>(op.b0(), op.q0(), tid, base) &
+                                                 loc_mask<T>(op.b1(), op.q1(), tid, base);
+                apply_signs<T, CT, W>(x, neg);
             }
             if (!kNoProducts && (hf & hbit(HB_ZSUM))) {
-                if (tid == 0) {
+                // every wavefront its part
+                if ((tid & 63) == 15) {
+                    const int wave = tid >> 6;
                     const double sg = ((base >> op.q0()) & 1u) ? -1.0 : 1.0;
 #pragma unroll
                     for (int b = 0; b < W; ++b) {
                         if (W > 1 && b < fa) continue;
-                        const int sl = op.slot() + b - fa;
-                        red[sl * kWaves] = make_double2(sg * Sr[b], sg * Si[b]);
-                        for (int k = 1; k < kWaves; ++k) red[sl * kWaves + k] = make_double2(0.0, 0.0);
+                        double2 v;
+                        if constexpr (TileSums<W>::kInLds) v = red[(kTileSumSlot + b) * kWaves + wave];
+                        else v = make_double2(ts.r[b], ts.i[b]);
+                        red[(op.slot() + b - fa) * kWaves + wave] = make_double2(sg * v.x, sg * v.y);
                     }
                 }
             }
@@ -1459,10 +1515,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
                 if (hf & hbit(HB_SEED)) {
                     // phi register op.aux (below the top one) <- sigma lambda;
                     // <lambda|phi> = <y|sigma|y> into the op's slot
-                    seed_handler<0, RB, T, CT, W>(x, op, tid, base, sink, red, zs, pass_zsum, Sr, Si);
+                    seed_handler<0, RB, T, CT, W>(x, op, tid, base, sink, red, pass_zsum, ts);
                     if constexpr (W > 2) {
-                        seed_handler<1, RB, T, CT, W>(x, op, tid, base, sink, red, zs, pass_zsum, Sr, Si);
-                        seed_handler<2, RB, T, CT, W>(x, op, tid, base, sink, red, zs, pass_zsum, Sr, Si);
+                        seed_handler<1, RB, T, CT, W>(x, op, tid, base, sink, red, pass_zsum, ts);
+                        seed_handler<2, RB, T, CT, W>(x, op, tid, base, sink, red, pass_zsum, ts);
                     }
                 }
             }
