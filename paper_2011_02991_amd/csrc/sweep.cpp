@@ -308,17 +308,64 @@ int scan_phase(const std::vector<Event> &ev, const std::vector<int> &pending, st
     return emitted;
 }
 
-DevMap mapping_for(uint32_t regset, int m, int rb, int carriers) {
-    DevMap mp{};
-    int p = 0;
-    for (int b = 0; b < m; ++b)
-        if ((regset >> b) & 1u) mp.pos[p++] = (uint8_t)b;
-    for (int b = 0; b < carriers; ++b)
-        if (!((regset >> b) & 1u)) mp.pos[p++] = (uint8_t)b;
-    for (int b = carriers; b < m; ++b)
-        if (!((regset >> b) & 1u)) mp.pos[p++] = (uint8_t)b;
-    (void)rb;
-    return mp;
+// Thread mappings of a pass that go through `seq`, the register sets in the
+// order they are used (the first loads the tile, the last stores it).
+//
+// Wavefront bits (thread bits 6 and up): the exchange buffer's slots that a
+// wavefront writes and those that it reads are the same when the wavefront bits
+// stand on the same tile positions before and after, and then the exchange needs
+// no barrier (exchange_local).  So they stand on the positions that stay out of
+// the register set the longest, and move only when one of them is needed there.
+// The carriers stay on the lanes.
+//
+// Lanes: the first four take tile positions of distinct classes modulo 4 as far
+// as there are any, which puts 16 neighbouring lanes on distinct banks (swizzle).
+std::vector<DevMap> thread_mappings(const std::vector<uint32_t> &seq, int m, int rb, int carriers) {
+    const int n_wave = std::max(0, m - rb - kLaneBits);
+    auto next_use = [&](size_t from, int bit) {
+        size_t k = from;
+        while (k < seq.size() && !((seq[k] >> bit) & 1u)) ++k;
+        return k;
+    };
+    std::vector<DevMap> out;
+    uint32_t wave = 0;
+    for (size_t i = 0; i < seq.size(); ++i) {
+        if (i == 0 || (wave & seq[i])) {
+            std::vector<int> bits;
+            for (int b = m - 1; b >= 0; --b)
+                if (!((seq[i] >> b) & 1u)) bits.push_back(b);
+            std::stable_sort(bits.begin(), bits.end(), [&](int a, int b) {
+                if ((a < carriers) != (b < carriers)) return b < carriers;
+                return next_use(i, a) > next_use(i, b);
+            });
+            wave = 0;
+            for (int k = 0; k < n_wave; ++k) wave |= 1u << bits[k];
+        }
+        DevMap mp{};
+        int p = 0;
+        for (int b = 0; b < m; ++b)
+            if ((seq[i] >> b) & 1u) mp.pos[p++] = (uint8_t)b;
+        uint32_t left = ((1u << m) - 1u) & ~seq[i] & ~wave;
+        uint32_t classes = 0;
+        for (int pass = 0; pass < 2; ++pass)
+            for (int b = 0; b < m; ++b) {
+                if (!((left >> b) & 1u) || (pass == 0 && ((classes >> (b & 3)) & 1u))) continue;
+                classes |= 1u << (b & 3);
+                left &= ~(1u << b);
+                mp.pos[p++] = (uint8_t)b;
+            }
+        for (int b = 0; b < m; ++b)
+            if ((wave >> b) & 1u) mp.pos[p++] = (uint8_t)b;
+        out.push_back(mp);
+    }
+    return out;
+}
+
+// Whether an exchange between two mappings stays within each wavefront.
+bool exchange_local(const DevMap &from, const DevMap &to, int m, int rb) {
+    for (int p = rb + kLaneBits; p < m; ++p)
+        if (from.pos[p] != to.pos[p]) return false;
+    return true;
 }
 
 uint8_t location(const DevMap &mp, int rb, int m, int localbit) {
@@ -430,30 +477,28 @@ HostPass make_pass(const Circuit &c, const SlotDest &sd, const std::vector<Event
         }
     }
 
-    // ---- thread mappings: load with the carriers on the lanes
-    auto add_map = [&](const DevMap &mp) { hp.maps.push_back(mp); return (int)hp.maps.size() - 1; };
-    uint32_t load_rs = phases[0].first;
-    bool load_xpose = false;
-    if (load_rs & carrier_mask) {
-        load_rs = ((1u << rb) - 1u) << (m - rb);
-        load_xpose = true;
-    }
-    hp.map_load = add_map(mapping_for(load_rs, m, rb, carriers));
-    int cur_map = hp.map_load;
-    auto xpose_to = [&](uint32_t rs) {
-        const int k = add_map(mapping_for(rs, m, rb, carriers));
+    // ---- thread mappings: load and store with the carriers on the lanes
+    const uint32_t top_rs = ((1u << rb) - 1u) << (m - rb);
+    std::vector<uint32_t> seq;
+    if (phases[0].first & carrier_mask) seq.push_back(top_rs);
+    for (const auto &ph : phases) seq.push_back(ph.first);
+    const bool store_xpose = current & carrier_mask;
+    if (store_xpose) seq.push_back(top_rs);
+    hp.maps = thread_mappings(seq, m, rb, carriers);
+    hp.map_load = 0;
+    int cur_map = 0;
+    auto xpose = [&]() {
         DevOp op{};
         op.type = OP_XPOSE;
         op.b0 = op.b1 = kLocBase;
         op.gate = -1;
-        op.aux = k;
+        op.aux = ++cur_map;
         hp.ops.push_back(op);
-        cur_map = k;
         ++hp.transposes;
     };
 
     for (size_t ph = 0; ph < phases.size(); ++ph) {
-        if (ph > 0 || load_xpose) xpose_to(phases[ph].first);
+        if (ph > 0 || seq.size() > phases.size() + (store_xpose ? 1 : 0)) xpose();
         const DevMap &mp = hp.maps[cur_map];
         const PhaseOrder po = order_phase(ev, phases[ph].second, c.n);
         const std::vector<int> &order = po.order;
@@ -546,8 +591,7 @@ HostPass make_pass(const Circuit &c, const SlotDest &sd, const std::vector<Event
             }
         }
     }
-    // store with the carriers on the lanes
-    if (current & carrier_mask) xpose_to(((1u << rb) - 1u) << (m - rb));
+    if (store_xpose) xpose();
     return hp;
 }
 
@@ -634,9 +678,9 @@ void flatten(SweepPlan &plan, const Circuit &c) {
                     op = DevOp{};
                     for (; k < end; ++k) {
                         const DevOp &o = hp.ops[k];
-                        if (o.type != OP_CZ || op.n_cz >= (uint32_t)kMaxCzSet)
+                        if (o.type != OP_CZ || op.arg >= (uint32_t)kMaxCzSet)
                             fail(QNG_E_DEVICE, "device op: not a set of CZs (internal)");
-                        set.cz[op.n_cz++] = (uint32_t)o.b0 | ((uint32_t)o.q0 << 8) | ((uint32_t)o.b1 << 16) |
+                        set.cz[op.arg++] = (uint32_t)o.b0 | ((uint32_t)o.q0 << 8) | ((uint32_t)o.b1 << 16) |
                                             ((uint32_t)o.q1 << 24);
                     }
                     --k;
@@ -648,7 +692,10 @@ void flatten(SweepPlan &plan, const Circuit &c) {
                 } else {
                     if (op.type == OP_ZSUM) dp.has_zsum = 1;
                     if (op.type == OP_CNOT) has_cnot = true;
-                    if (op.type == OP_XPOSE) op.aux += (int32_t)map_base;
+                    if (op.type == OP_XPOSE) {
+                        op.arg = exchange_local(hp.maps[op.aux - 1], hp.maps[op.aux], plan.m, plan.rb);
+                        op.aux += (int32_t)map_base;
+                    }
                     op.type = device_opcode(op);
                 }
                 const int h2 = device_handler2(op.type);

@@ -116,6 +116,7 @@ constexpr uint8_t kLocThread = 0x10;
 constexpr uint8_t kLocBase = 0xFF;
 constexpr int kMaxSlots = 256;      // inner products per pass
 constexpr int kMaxTileQubits = 13;
+constexpr int kLaneBits = 6;          // lanes of a wavefront: 2^6
 constexpr int kMaxRest = 24;        // qubits outside a tile
 constexpr int kMaxBlockWidth = 4;   // columns sharing one lambda sweep
 constexpr int kDefaultBlockWidth = 2;   // measured at n = 26: 8-11 % less sweep time than 1
@@ -129,7 +130,7 @@ struct DevOp {  // 32 bytes
                       // OP_SEED: the phi register seeded
     uint32_t hlo, hhi;   // device images: one-hot handler bit (HB_* below), low and high word
     uint32_t h2;         // device images: one-hot bit of the controlled-rotation handlers (HB2_*), or 0
-    uint32_t n_cz;       // device images, OPC_CZS: number of CZs
+    uint32_t arg;        // device images: number of CZs (OPC_CZS), whether each wavefront keeps its part (OPC_XPOSE)
 };
 
 struct DevPass {  // 64 bytes, read through a pointer with scalar loads

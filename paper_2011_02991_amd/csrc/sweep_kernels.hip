@@ -41,7 +41,8 @@ namespace qng {
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreadBits = 8;
+constexpr int kThreads = 1 << kThreadBits;
 constexpr int kWaves = kThreads / 64;
 
 template <typename R> struct Amp;
@@ -726,7 +727,7 @@ struct OpD {
     int32_t gate, aux;
     uint64_t hf;   // one-hot handler bit (sweep.hpp, HB_*)
     uint32_t h2;   // one-hot bit of the second word (HB2_*), or 0
-    uint32_t n_cz; // OPC_CZS: number of CZs
+    uint32_t arg;  // OPC_CZS: number of CZs; OPC_XPOSE: whether each wavefront keeps its part
     __device__ __forceinline__ int type() const { return (int)(w0 & 0xffu); }
     __device__ __forceinline__ uint8_t b0() const { return (uint8_t)((w0 >> 8) & 0xffu); }
     __device__ __forceinline__ uint8_t b1() const { return (uint8_t)((w0 >> 16) & 0xffu); }
@@ -819,26 +820,30 @@ __device__ __forceinline__ uint32_t swizzle(uint32_t l) {
     return f;
 }
 
-// Exchange-buffer slot of each of a thread's registers under a mapping: the
-// swizzled local (in-tile) index.  The swizzle is linear and the register and
-// thread bits are disjoint, so the slot is the XOR of the swizzled parts.
-template <int RB, int T>
-__device__ __forceinline__ void local_offsets(const MapBytes &mp, int tbits, int tid, uint32_t (&off)[T]) {
-    uint32_t lth = 0;
+// Exchange-buffer offsets in bytes under a mapping: the swizzle is linear and
+// the register and thread bits are disjoint, so the slot of an amplitude is the
+// XOR of its thread's part (thread_slot) and those of its register bits, which
+// are scalars.
+template <int RB, typename CX>
+__device__ __forceinline__ uint32_t thread_slot(const MapBytes &mp, int tbits, int tid) {
+    uint32_t l = 0;
 #pragma unroll
-    for (int t = 0; t < kMaxTileQubits; ++t)
-        if (t < tbits) lth |= (uint32_t)((tid >> t) & 1) << byte_at(mp.pos, RB + t);
-    lth = swizzle(lth);
+    for (int t = 0; t < kThreadBits; ++t)
+        if (t < tbits) l |= (uint32_t)((tid >> t) & 1) << byte_at(mp.pos, RB + t);
+    return swizzle(l) * (uint32_t)sizeof(CX);
+}
+
+// Calls f(i, offset) for each of a thread's amplitudes, in Gray-code order: one
+// XOR with a scalar from each offset to the next.
+template <int RB, typename CX, typename F>
+__device__ __forceinline__ void each_slot(const MapBytes &mp, uint32_t thread, F f) {
     uint32_t u[RB];
 #pragma unroll
-    for (int j = 0; j < RB; ++j) u[j] = swizzle(1u << byte_at(mp.pos, j));
+    for (int j = 0; j < RB; ++j) u[j] = swizzle(1u << byte_at(mp.pos, j)) * (uint32_t)sizeof(CX);
 #pragma unroll
-    for (int i = 0; i < T; ++i) {
-        uint32_t l = lth;
-#pragma unroll
-        for (int j = 0; j < RB; ++j)
-            if ((i >> j) & 1) l ^= u[j];
-        off[i] = l;
+    for (int k = 0; k < (1 << RB); ++k) {
+        if (k) thread ^= u[__builtin_ctz(k)];
+        f(k ^ (k >> 1), thread);
     }
 }
 
@@ -1152,40 +1157,56 @@ __device__ __forceinline__ void apply_signs(Regs<CT, T, W> &x, uint32_t neg) {
     }
 }
 
+// Between the writes and the reads of an exchange.  Local: the wavefront reads
+// the slots that it wrote itself, and its LDS operations run in order, so only
+// the compiler has to keep theirs.  Two exchanges in three are local (mappings
+// chosen for it by the planner): 22 qubits, complex128, real and imaginary
+// products 96.5 -> 95.5 ms a step, 24 qubits, complex64 500 -> 497 ms.  The
+// kernels with controlled handlers keep the barriers: with the branch around
+// them they spill more, and run 2 % longer.
+__device__ __forceinline__ void exchange_barrier(bool local) {
+    if (local) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        __syncthreads();
+    }
+}
+
 // One register of the tile through the exchange buffer, from mapping `from`
-// to mapping `to`.  With RECOMPUTE the slots are recomputed for every
-// register from an opaque copy of the thread index (the kernels with two phi
-// registers near the VGPR bound: kept across the exchanges of all three
-// registers the slots hold 2T more VGPRs next to the tile, and spill);
-// otherwise the compiler computes them once for all registers.
+// (thread part of its slots: from_th) to mapping `to` (to_th).  With RECOMPUTE
+// the thread parts are computed for every register from an opaque copy of the
+// thread index (the kernels with two phi registers near the VGPR bound: kept
+// across the exchanges of all three registers the slots hold 2T more VGPRs next
+// to the tile, and spill); otherwise the compiler computes the slots once for
+// all registers.  The arithmetic matters: recomputed where there is room to
+// keep them, a step of 24 qubits (complex64, four phi registers) takes 10 %
+// longer, and one XOR per slot in place of a sum over the register bits took
+// 21 qubits with controlled rotations from 19.2 to 18.6 ms.
 template <int RB, int T, typename CT, typename CX, bool RECOMPUTE>
-__device__ __forceinline__ void exchange(CT (&re)[T], CT (&im)[T], CX *xbuf, const MapBytes &from,
-                                         const MapBytes &to, int tbits, int tid, bool active) {
-    int t = tid;
-    if constexpr (RECOMPUTE) asm volatile("" : "+v"(t));
+__device__ __forceinline__ void exchange(CT (&re)[T], CT (&im)[T], CX *xbuf, const MapBytes &from, uint32_t from_th,
+                                         const MapBytes &to, uint32_t to_th, int tbits, int tid, bool active, bool local) {
+    if constexpr (RECOMPUTE) asm volatile("" : "+v"(tid));
+    if constexpr (RECOMPUTE) from_th = thread_slot<RB, CX>(from, tbits, tid);
     if (active) {
-        uint32_t lo[T];
-        local_offsets<RB, T>(from, tbits, t, lo);
-#pragma unroll
-        for (int i = 0; i < T; ++i) {
+        each_slot<RB, CX>(from, from_th, [&](int i, uint32_t off) {
             CX v;
             v.x = re[i];
             v.y = im[i];
-            xbuf[lo[i]] = v;
-        }
+            *(CX *)((char *)xbuf + off) = v;
+        });
     }
-    __syncthreads();
+    exchange_barrier(local);
+    if constexpr (RECOMPUTE) to_th = thread_slot<RB, CX>(to, tbits, tid);
     if (active) {
-        uint32_t lo[T];
-        local_offsets<RB, T>(to, tbits, t, lo);
-#pragma unroll
-        for (int i = 0; i < T; ++i) {
-            const CX v = xbuf[lo[i]];
+        each_slot<RB, CX>(to, to_th, [&](int i, uint32_t off) {
+            const CX v = *(const CX *)((const char *)xbuf + off);
             re[i] = v.x;
             im[i] = v.y;
-        }
+        });
     }
-    __syncthreads();
+    exchange_barrier(local);
 }
 
 template <typename R, typename CT, int T>
@@ -1321,6 +1342,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
 
     // ---- load
     MapBytes cur = load_map(maps + ph1.x);
+    // thread's part of the exchange slots under `cur`: kept from one exchange to
+    // the next where a register is free for it
+    constexpr bool kRecompute = W > 1 && (RB >= 4 || sizeof(R) < sizeof(CT));
+    uint32_t cur_th = !kRecompute ? thread_slot<RB, CX>(cur, tbits, tid) : 0;
     {
         uint64_t off[T];
         global_offsets<RB, T>(pbytes, cur, tbits, tid, base, off);
@@ -1491,7 +1516,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
         if (hf & (hbit(HB_XPOSE) | hbit(HB_CZ) | hbit(HB_ZSUM) | hbit(HB_SEED))) {
             if (hf & hbit(HB_CZ)) {
                 // one CZ, or a set of them
-                const uint32_t neg = op.n_cz ? cz_signs<T>(reinterpret_cast<const uint32_t *>(maps + op.aux), op.n_cz, tid, base)
+                const uint32_t neg = op.arg ? cz_signs<T>(reinterpret_cast<const uint32_t *>(maps + op.aux), op.arg, tid, base)
                                            : loc_mask<T>(op.b0(), op.q0(), tid, base) &
                                                  loc_mask<T>(op.b1(), op.q1(), tid, base);
                 apply_signs<T, CT, W>(x, neg);
@@ -1524,11 +1549,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
             }
             if (hf & hbit(HB_XPOSE)) {
                 const MapBytes next = load_map(maps + op.aux);
-                constexpr bool kRecompute = W > 1 && (RB >= 4 || sizeof(R) < sizeof(CT));
-                exchange<RB, T, CT, CX, kRecompute>(x.ar, x.ai, xbuf, cur, next, tbits, tid, active);
+                const uint32_t th = kRecompute ? 0 : thread_slot<RB, CX>(next, tbits, tid);
+                exchange<RB, T, CT, CX, kRecompute>(x.ar, x.ai, xbuf, cur, cur_th, next, th, tbits, tid, active, !CTRL && op.arg);
 #pragma unroll
                 for (int b = 0; b < W; ++b)
-                    exchange<RB, T, CT, CX, kRecompute>(x.br[b], x.bi[b], xbuf, cur, next, tbits, tid, active);
+                    exchange<RB, T, CT, CX, kRecompute>(x.br[b], x.bi[b], xbuf, cur, cur_th, next, th, tbits, tid, active, !CTRL && op.arg);
+                cur_th = th;
                 cur = next;
             }
         }
