@@ -43,10 +43,21 @@ struct Group {
     size_t launch_begin = 0, launch_end = 0;
 };
 
+// Whether the forward register's gates and the column starts run as one launch
+// per group with the state in LDS (not in the derivative-state variant): wherever
+// it fits.  Four layers of RY, RZ and a CNOT chain, metric, launches per column
+// against the chain: 2 qubits 285 -> 160 us, 10 qubits 735 -> 310 us, 13 qubits
+// 800 -> 670 us (complex128), 14 qubits 850 -> 780 us (complex64).
+bool use_chain(int n, size_t amp_bytes) { return n <= chain_qubits(amp_bytes); }
+
 }  // namespace
 
 size_t fused_scratch_bytes(const SweepPlan &plan, const FusedRun &fr, int M) {
     size_t b = 0;
+    if (plan.n <= chain_qubits(8)) {
+        b += align256((size_t)(2 * M + 2 * plan.P + 8) * sizeof(ChainStep) + 64);   // a gate and a DOT each at most
+        b += align256((plan.cols.size() + 1) * (sizeof(ChainItem) + sizeof(PhiItem)) + 128);
+    }
     b += align256((size_t)M * 64 + 64);                                  // matrix table (FP64)
     b += align256((size_t)M * 32 + 64);                                  // matrix table (FP32)
     b += align256((size_t)M * 64 + 64);                                  // forward matrices (FP64)
@@ -168,6 +179,11 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
         adjoint_row(r.axis, r.ctrl >= 0, adj[r.pos], &mats[(size_t)r.pos * 8]);
     }
     fill_fixed_shears(c, adj, mats);
+    for (int pos = 0; pos < c.M; ++pos) {
+        if (!c.is_fixed_rotation(pos)) continue;
+        const DevMat2 m = to_dev(fwd[pos]);
+        std::memcpy(&fmats[(size_t)pos * 8], &m, sizeof m);
+    }
     std::vector<float> mats32(mats.begin(), mats.end());
     char *p = buf.scratch;
     auto take = [&](size_t bytes) { char *o = p; p += align256(bytes + 64); return o; };
@@ -193,7 +209,8 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
     // gate with cos(theta/2) < 0 is applied negated (as in the sweeps), so psi
     // may carry a sign; every product and T, E and the gradient are quadratic
     // in it, and psi is put right at the end of the metric phase.
-    const SweepPlan *fp = plan.forward ? plan.forward.get() : nullptr;
+    const bool chain = !states && use_chain(n, V >> n);
+    const SweepPlan *fp = plan.forward && !chain ? plan.forward.get() : nullptr;
     std::vector<double> fshear;
     std::vector<LaunchItem> fitems;
     std::vector<uint8_t> seg_neg;
@@ -235,6 +252,64 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
         d_fitems = (LaunchItem *)take(fitems.size() * sizeof(LaunchItem));
     }
     std::vector<float> fshear32(fshear.begin(), fshear.end());
+    // the chain: one item per group (the first with the gates before rotation 0
+    // and its T), then the starts of the group's columns
+    std::vector<ChainStep> csteps;
+    std::vector<ChainItem> citems;
+    std::vector<PhiItem> phis;
+    ChainStep *d_csteps = nullptr;
+    ChainItem *d_citems = nullptr;
+    PhiItem *d_phis = nullptr;
+    int chain_end = 0;
+    if (chain) {
+        std::vector<uint8_t> diag((size_t)c.P, 0);
+        auto dot = [&](int q, int axis, int ctrl, double *dest) {
+            csteps.push_back(ChainStep{nullptr, nullptr, dest, CHAIN_DOT, q, ctrl, axis});
+        };
+        auto diag_of = [&](int r) {
+            const int ctrl = c.rots[r].ctrl;
+            if (ctrl < 0 || diag[r]) return;
+            diag[r] = 1;
+            dot(ctrl == 0 ? 1 : 0, -1, ctrl, buf.lraw + 2 * ((size_t)r * c.P + r));
+        };
+        auto gates_to = [&](int target) {
+            for (; chain_end < target; ++chain_end) {
+                const qng_gate &g = c.gates[chain_end];
+                const double *m = d_fmats + (size_t)chain_end * 8;
+                if (g.kind >= QNG_CRX && g.kind <= QNG_CRZ) {
+                    diag_of(c.rot_at[chain_end]);
+                    csteps.push_back(ChainStep{m, nullptr, nullptr, CHAIN_GATE, g.q1, g.q0, 0});
+                } else if (g.kind == QNG_CNOT || g.kind == QNG_CZ) {
+                    csteps.push_back(ChainStep{nullptr, nullptr, nullptr, g.kind == QNG_CNOT ? CHAIN_CNOT : CHAIN_CZ,
+                                               g.q1, g.q0, 0});
+                } else {
+                    csteps.push_back(ChainStep{m, nullptr, nullptr, CHAIN_GATE, g.q0, -1, 0});
+                }
+            }
+        };
+        std::vector<size_t> first(1, 0);
+        gates_to(c.rots[0].pos);
+        dot(c.rots[0].qubit, c.rots[0].axis, c.rots[0].ctrl, buf.traw);
+        diag_of(0);
+        for (const Group &G : groups) {
+            for (int col = G.col_begin; col < G.col_end; ++col) {
+                const int s = plan.cols[col].s, b = col - G.col_begin;
+                const Rot &rs = c.rots[s];
+                gates_to(rs.pos);
+                if (csteps.back().kind == CHAIN_DOT) fail(QNG_E_DEVICE, "chain: no gate before a column (internal)");
+                csteps.back().store = reg(b, 0);
+                phis.push_back(PhiItem{reg(b, 0), xi_of(s, b, W - 1), buf.traw + 2 * s, n, rs.qubit, rs.axis, rs.ctrl});
+                diag_of(s);
+            }
+            first.push_back(csteps.size());
+        }
+        if (groups.empty()) first.push_back(csteps.size());
+        d_csteps = (ChainStep *)take(csteps.size() * sizeof(ChainStep));
+        d_citems = (ChainItem *)take((first.size() - 1) * sizeof(ChainItem));
+        d_phis = (PhiItem *)take(phis.size() * sizeof(PhiItem));
+        for (size_t g = 0; g + 1 < first.size(); ++g)
+            citems.push_back(ChainItem{state(0), d_csteps + first[g], (int32_t)(first[g + 1] - first[g]), n});
+    }
     double *d_partials = (double *)p;
     if ((size_t)(p - buf.scratch) + fr.partial_elems * 16 > buf.scratch_bytes)
         fail(QNG_E_DEVICE, "fused sweep: scratch too small (internal)");
@@ -257,6 +332,12 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
         FCHECK(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(LaunchItem), hipMemcpyHostToDevice, st));
     if (!tasks.empty())
         FCHECK(hipMemcpyAsync(d_tasks, tasks.data(), tasks.size() * sizeof(ReduceTask), hipMemcpyHostToDevice, st));
+    if (chain) {
+        FCHECK(hipMemcpyAsync(d_csteps, csteps.data(), csteps.size() * sizeof(ChainStep), hipMemcpyHostToDevice, st));
+        FCHECK(hipMemcpyAsync(d_citems, citems.data(), citems.size() * sizeof(ChainItem), hipMemcpyHostToDevice, st));
+        if (!phis.empty())
+            FCHECK(hipMemcpyAsync(d_phis, phis.data(), phis.size() * sizeof(PhiItem), hipMemcpyHostToDevice, st));
+    }
     if (fp) {
         FCHECK(hipMemcpyAsync(d_fsh, fshear.data(), fshear.size() * 8, hipMemcpyHostToDevice, st));
         FCHECK(hipMemcpyAsync(d_fsh32, fshear32.data(), fshear32.size() * 4, hipMemcpyHostToDevice, st));
@@ -327,8 +408,11 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
             ++stats->other_launches;
         }
     };
-    forward_to(c.rots[0].pos, nullptr);
-    if (states) {
+    if (!chain) forward_to(c.rots[0].pos, nullptr);
+    if (chain) {
+        if (groups.empty()) launch_chain<R>(d_citems, 1, n, st);
+        pos = chain_end;
+    } else if (states) {
         // the sweeps end in the frame just after rotation 0 (its adjoint is never
         // applied): lambda* = R_0 y_0 there, and column 0's derivative state is
         // sigma_0 lambda* (R_0 commutes with sigma_0)
@@ -349,7 +433,7 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
                              c.rots[0].ctrl);
         control_diag(0);
     }
-    stats->other_launches += 2;
+    stats->other_launches += chain ? (groups.empty() ? 1 : 0) : 2;
     uint8_t psi_negated = 0;
     // segment k of the forward plan takes psi from the top of block k - 1 (from
     // rotation 0 for k = 0) to the top of block k; psi is at the start of
@@ -366,7 +450,12 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
         return (fix ? d_nfmats : d_fmats) + (size_t)gate_pos * 8;
     };
     for (const Group &G : groups) {
-        for (int col = G.col_begin; col < G.col_end; ++col) {
+        if (chain) {
+            launch_chain<R>(d_citems + (&G - groups.data()), 1, n, st);
+            launch_phi<R>(d_phis + (G.col_begin - blk_begin), G.col_end - G.col_begin, st);
+            stats->other_launches += 2;
+        }
+        for (int col = chain ? G.col_end : G.col_begin; col < G.col_end; ++col) {
             const int s = plan.cols[col].s;    // top column of the block
             const Rot &rs = c.rots[s];
             const Rot &rp = c.rots[s - 1];

@@ -485,6 +485,139 @@ __global__ void k_advance_seed(typename Cplx<R>::T *psi, typename Cplx<R>::T *la
     block_reduce_store(sr, si, partials + 2 * blockIdx.x);
 }
 
+// The forward register's steps (ChainStep) with the state in LDS, one
+// work-group per item.  A step is one read and one write of the state in LDS and
+// a barrier (0.5 us at 10 qubits in complex128); as launches of their own a
+// column took two, 4 us each with the gaps.  A step of 10 qubits, 80
+// parameters: 928 -> 500 us.  The steps are
+// copied to LDS a chunk at a time, so the loop loads nothing from memory and
+// the stores of a state's copies need not be waited for.
+constexpr int kChainThreads = 1024;
+constexpr int kChainChunk = 64;
+
+template <typename R>
+__global__ __launch_bounds__(kChainThreads) void k_chain(const ChainItem *__restrict__ items) {
+    using C = typename Cplx<R>::T;
+    extern __shared__ __align__(16) unsigned char chain_lds[];
+    __shared__ ChainStep steps[kChainChunk];
+    __shared__ double mats[kChainChunk * 8];
+    __shared__ double part[2 * kChainThreads / 64];
+    C *x = (C *)chain_lds;
+    const ChainItem it = items[blockIdx.x];
+    C *const psi = (C *)it.psi;
+    const int dim = 1 << it.n, npairs = dim >> 1;
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    for (int i = tid; i < dim; i += nthr) x[i] = psi[i];
+    for (int s0 = 0; s0 < it.n_steps; s0 += kChainChunk) {
+        const int ns = it.n_steps - s0 < kChainChunk ? it.n_steps - s0 : kChainChunk;
+        __syncthreads();
+        for (int k = tid; k < ns; k += nthr) steps[k] = it.steps[s0 + k];
+        for (int k = tid; k < ns * 8; k += nthr) {
+            const double *m = it.steps[s0 + (k >> 3)].m;
+            if (m) mats[k] = m[k & 7];
+        }
+        __syncthreads();
+        for (int k = 0; k < ns; ++k) {
+            const int kind = __builtin_amdgcn_readfirstlane(steps[k].kind);
+            const int q = __builtin_amdgcn_readfirstlane(steps[k].q);
+            const int ctrl = __builtin_amdgcn_readfirstlane(steps[k].ctrl);
+            if (kind == CHAIN_DOT) {
+                const int axis = steps[k].axis;
+                double sr = 0.0, si = 0.0;
+                for (int p = tid; p < npairs; p += nthr) {
+                    const int i0 = (int)insert_zero((uint64_t)p, q), i1 = i0 | (1 << q);
+                    if (ctrl >= 0 && !((i0 >> ctrl) & 1)) continue;
+                    const C u = x[i0], v = x[i1];
+                    C o0 = u, o1 = v;
+                    if (axis >= 0) pauli_pair(axis, u, v, o0, o1);
+                    cmac(sr, si, u.x, u.y, o0.x, o0.y);
+                    cmac(sr, si, v.x, v.y, o1.x, o1.y);
+                }
+                for (int w = 32; w > 0; w >>= 1) {
+                    sr += __shfl_xor(sr, w);
+                    si += __shfl_xor(si, w);
+                }
+                if ((tid & 63) == 0) {
+                    part[2 * (tid >> 6)] = sr;
+                    part[2 * (tid >> 6) + 1] = si;
+                }
+                __syncthreads();
+                if (tid == 0) {
+                    double tr = 0.0, ti = 0.0;
+                    for (int w = 0; w < nthr / 64; ++w) {
+                        tr += part[2 * w];
+                        ti += part[2 * w + 1];
+                    }
+                    double *d = steps[k].dot;
+                    d[0] = tr;
+                    d[1] = ti;
+                }
+                __syncthreads();
+                continue;
+            }
+            C *const store = (C *)steps[k].store;
+            R ar = 0, ai = 0, br = 0, bi = 0, cr = 0, ci = 0, dr = 0, di = 0;
+            if (kind == CHAIN_GATE) {
+                const double *m = mats + 8 * k;
+                ar = (R)m[0]; ai = (R)m[1]; br = (R)m[2]; bi = (R)m[3];
+                cr = (R)m[4]; ci = (R)m[5]; dr = (R)m[6]; di = (R)m[7];
+            }
+            for (int p = tid; p < npairs; p += nthr) {
+                const int i0 = (int)insert_zero((uint64_t)p, q), i1 = i0 | (1 << q);
+                C u = x[i0], v = x[i1];
+                if (ctrl < 0 || ((i0 >> ctrl) & 1)) {
+                    const C a = u, b = v;
+                    if (kind == CHAIN_GATE) {
+                        u.x = ar * a.x - ai * a.y + br * b.x - bi * b.y;
+                        u.y = ar * a.y + ai * a.x + br * b.y + bi * b.x;
+                        v.x = cr * a.x - ci * a.y + dr * b.x - di * b.y;
+                        v.y = cr * a.y + ci * a.x + dr * b.y + di * b.x;
+                    } else if (kind == CHAIN_CNOT) {
+                        u = b;
+                        v = a;
+                    } else {
+                        v.x = -b.x;
+                        v.y = -b.y;
+                    }
+                    x[i0] = u;
+                    x[i1] = v;
+                }
+                if (store) {
+                    store[i0] = u;
+                    store[i1] = v;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < dim; i += nthr) psi[i] = x[i];
+}
+
+// One work-group per column: the phi register and T of a column whose lambda
+// register the chain wrote (PhiItem), all columns of a group in one launch.
+template <typename R>
+__global__ __launch_bounds__(kBlock) void k_phi(const PhiItem *__restrict__ items) {
+    using C = typename Cplx<R>::T;
+    const PhiItem it = items[blockIdx.x];
+    const C *lam = (const C *)it.lam;
+    C *phi = (C *)it.phi;
+    const int npairs = 1 << (it.n - 1);
+    double sr = 0.0, si = 0.0;
+    for (int p = threadIdx.x; p < npairs; p += kBlock) {
+        const int i0 = (int)insert_zero((uint64_t)p, it.q), i1 = i0 | (1 << it.q);
+        const C u = lam[i0], v = lam[i1];
+        C o0, o1;
+        pauli_pair(it.axis, u, v, o0, o1);
+        if (it.ctrl >= 0 && !((i0 >> it.ctrl) & 1)) o0.x = o0.y = o1.x = o1.y = 0;
+        phi[i0] = o0;
+        phi[i1] = o1;
+        cmac(sr, si, u.x, u.y, o0.x, o0.y);
+        cmac(sr, si, v.x, v.y, o1.x, o1.y);
+    }
+    block_reduce_store(sr, si, it.dot);
+}
+
 // Column seeds of many registers in one launch (the batched metric): item k
 // applies up to two forward rotations (qa then qb; -1: none) to its register
 // psi, then writes lam = psi, phi = sigma_qs psi and its work-groups' partial
@@ -1144,6 +1277,26 @@ void launch_seed_multi(const SeedItem *items, int n_items, uint32_t total_blocks
     check_launch();
 }
 
+template <typename R> void launch_chain(const ChainItem *items, int n_items, int max_n, hipStream_t st) {
+    if (n_items <= 0) return;
+    if (max_n < 1 || max_n > chain_qubits(sizeof(typename Cplx<R>::T))) throw hipErrorInvalidValue;
+    const size_t lds = sizeof(typename Cplx<R>::T) << max_n;
+    if (lds > 32768) {
+        const hipError_t e = hipFuncSetAttribute((const void *)k_chain<R>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)lds);
+        if (e != hipSuccess) throw e;
+    }
+    const int threads = std::min(kChainThreads, std::max(64, 1 << (max_n - 1)));
+    hipLaunchKernelGGL(k_chain<R>, dim3(n_items), dim3(threads), lds, st, items);
+    check_launch();
+}
+
+template <typename R> void launch_phi(const PhiItem *items, int n_items, hipStream_t st) {
+    if (n_items <= 0) return;
+    hipLaunchKernelGGL(k_phi<R>, dim3(n_items), dim3(kBlock), 0, st, items);
+    check_launch();
+}
+
 template <typename R>
 void launch_advance2_seed(void *psi, void *lam, void *phi, int n, int qa, const double *ma, int qb, const double *mb,
                           int qc, int axis, double *partials, double *dest, hipStream_t st) {
@@ -1269,6 +1422,8 @@ void launch_grad_from_raw(const double *graw, const int *param_of, int P, double
     template void launch_seed_multi<R>(const SeedItem *, int, uint32_t, double *, hipStream_t);                      \
     template void launch_pauli_term<R>(const void *, void *, int, uint64_t, uint64_t, int, double, int, hipStream_t); \
     template void launch_pauli_sum<R>(const void *, void *, int, const HamTerm *, int, double *, double *, hipStream_t); \
+    template void launch_chain<R>(const ChainItem *, int, int, hipStream_t);                                       \
+    template void launch_phi<R>(const PhiItem *, int, hipStream_t);                                                \
     template void launch_advance2_seed<R>(void *, void *, void *, int, int, const double *, int, const double *, int, \
                                           int, double *, double *, hipStream_t);
 

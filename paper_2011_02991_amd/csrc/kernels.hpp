@@ -125,6 +125,35 @@ template <typename R>
 void launch_advance2_seed(void *psi, void *lam, void *phi, int n, int qa, const double *ma, int qb, const double *mb,
                           int qc, int axis, double *partials, double *dest, hipStream_t st);
 
+// The forward register's way through the gates with the state in LDS, for
+// registers of at most chain_qubits(): one work-group per register takes every
+// step in turn; a step with `store` leaves a copy of the state after it there.
+enum { CHAIN_GATE = 0, CHAIN_CNOT = 1, CHAIN_CZ = 2, CHAIN_DOT = 3 };
+struct ChainStep {
+    const double *m;   // CHAIN_GATE: the matrix (8 doubles, a, b, c, d as re, im), device
+    void *store;       // copy of the state after this step, or nullptr
+    double *dot;       // CHAIN_DOT: <psi|sigma_q|psi> (axis -1: the identity), one complex128
+    int32_t kind, q, ctrl, axis;   // ctrl >= 0: only amplitudes with that bit set (never q itself)
+};
+struct ChainItem {
+    void *psi;         // read first, written last
+    const ChainStep *steps;
+    int32_t n_steps, n;
+};
+// Start of a column whose lambda register is written: phi = K lam, dot = <lam|phi>
+// with K = sigma_q (ctrl >= 0: |1><1|_ctrl (x) sigma_q).
+struct PhiItem {
+    const void *lam;
+    void *phi;
+    double *dot;
+    int32_t n, q, axis, ctrl;
+};
+// Largest register that the chain takes: 128 KB of LDS.
+constexpr int chain_qubits(size_t amp_bytes) { return amp_bytes >= 16 ? 13 : 14; }
+// max_n: the largest n among the items
+template <typename R> void launch_chain(const ChainItem *items, int n_items, int max_n, hipStream_t st);
+template <typename R> void launch_phi(const PhiItem *items, int n_items, hipStream_t st);
+
 // dest (one complex128) = <a| sigma_q |b>; axis -1 means the identity (plain inner product).
 // ctrl >= 0: <a| |1><1|_ctrl (x) sigma_q |b> (only amplitudes with bit ctrl = 1).
 // partials: reduce_blocks(n) complex128 scratch.
