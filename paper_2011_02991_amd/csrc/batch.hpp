@@ -41,6 +41,28 @@ struct BatchPrep {              // admission of column block `col` of `member` i
 struct BatchLaunch {
     uint32_t item_begin, n_items, total_tiles, task_begin, n_tasks, prep_begin, n_preps;
     uint32_t round_begin, n_rounds;   // the launch's column seeds, in rounds
+    uint32_t chain_begin, n_chains, phi_begin, n_phis;   // those of the small members
+    int chain_max_n;
+};
+
+// The column seeds of members whose register fits the chain kernel (state in
+// LDS): before a launch, one work-group per member takes its gates up to the last
+// of its columns in the launch and leaves lambda at each; then one per column
+// forms phi and T.
+struct BatchChainStep {
+    int kind, q, ctrl, axis;
+    int64_t mat_row, dot;     // row of the matrix table, complex of the raw L and T (-1: none)
+    uint64_t store_off;       // arena offset of the state's copy (kNoStore: none)
+};
+constexpr uint64_t kNoStore = ~uint64_t(0);
+struct BatchChain {
+    int member;
+    uint32_t step_begin, n_steps;
+};
+struct BatchPhi {
+    int member, q, axis, ctrl;
+    uint64_t lam_off, phi_off;
+    int64_t dot;
 };
 
 // The column seeds before a launch go in rounds: a round holds at most one
@@ -81,6 +103,9 @@ struct BatchSchedule {
     std::vector<BatchPrep> preps;
     std::vector<BatchSeed> seeds;
     std::vector<BatchRound> rounds;
+    std::vector<BatchChainStep> chain_steps;
+    std::vector<BatchChain> chains;
+    std::vector<BatchPhi> phis;
     std::vector<ReduceTask> seed_tasks;                      // per seed: its T from the round's partials
     std::vector<BatchLaunch> launches;
     std::vector<int> singles;                                // members with P == 1 (no columns)

@@ -52,3 +52,24 @@ def test_chain(env, kind, n, gates, prec, streams):
         err = np.abs(res[key] - want[key]).max() / scale
         print(kind, n, gates, prec, streams, key, err, "tol", tol, flush=True)
         assert err <= tol
+
+
+@pytest.mark.parametrize("tiles", [1, 0])
+def test_chain_batched(env, tiles):
+    """Members below, at and above the chain's largest register, in one batch;
+    one launch per column block (tiles 1) and as many as fit."""
+    q, ctx = env
+    prs = [problem(kind, n, gates, 9500 + n + gates) for kind, n, gates in
+           (("plain", 1, 4), ("controlled", 5, 70), ("plain", 8, 66), ("strings", 9, 20), ("plain", 13, 40),
+            ("controlled", 13, 40), ("plain", 14, 40))]
+    ctx.set_option(q.OPT_BATCH_TILES, tiles)
+    try:
+        res = ctx.step_batched([q.Circuit.from_problem(p) for p in prs], [p.theta for p in prs], 0.1, 1e-4)
+    finally:
+        ctx.set_option(q.OPT_BATCH_TILES, 0)
+    for p, r in zip(prs, res):
+        want = oracle.step(p)
+        for key, scale in (("G", np.abs(want["G"]).max()), ("grad", np.abs(p.coeff).sum())):
+            err = np.abs(r[key] - want[key]).max() / scale
+            print(p.name, tiles, key, err, flush=True)
+            assert err <= 1e-10
