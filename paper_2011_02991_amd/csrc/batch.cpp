@@ -263,6 +263,8 @@ BatchSchedule build_batch_schedule(const std::vector<const Circuit *> &members,
         std::copy(others.begin(), others.end(), S.preps.begin() + L.prep_begin);
         L.n_preps = (uint32_t)others.size();
         L.round_begin = (uint32_t)S.rounds.size();
+        L.seed_task_begin = (uint32_t)S.seed_tasks.size();
+        uint32_t sums = 0;   // the rounds' work-group sums, kept until the launch's one reduction of T
         std::map<int, int> seen;
         std::vector<int> ridx(L.n_preps);
         int nr = 0;
@@ -271,7 +273,7 @@ BatchSchedule build_batch_schedule(const std::vector<const Circuit *> &members,
             nr = std::max(nr, ridx[k] + 1);
         }
         for (int r = 0; r < nr; ++r) {
-            BatchRound R{(uint32_t)S.seeds.size(), 0, 0, 0};
+            BatchRound R{(uint32_t)S.seeds.size(), 0, 0, sums, 0};
             // the one kernel's items first (registers of >= 3 qubits, no controlled
             // rotation at the seed), then the seeds run on their own
             auto multi = [&](uint32_t k) {
@@ -322,20 +324,21 @@ BatchSchedule build_batch_schedule(const std::vector<const Circuit *> &members,
                     sd.nblocks = (uint32_t)std::min<uint64_t>(kSeedBlocksMax, (groups + 255) / 256);
                     sd.block_begin = R.total_blocks;
                     R.total_blocks += sd.nblocks;
-                    S.seed_tasks.push_back(ReduceTask{(uint64_t)sd.block_begin, sd.nblocks,
+                    S.seed_tasks.push_back(ReduceTask{(uint64_t)sums + sd.block_begin, sd.nblocks,
                                                       (int32_t)(S.lraw_base[pr.member] + (int64_t)c.P * c.P + sidx)});
                     ++R.n_multi;
                 } else {
-                    sd.nblocks = 0;   // seeded on its own; its task is never launched
-                    S.seed_tasks.push_back(ReduceTask{0, 0, 0});
+                    sd.nblocks = 0;   // seeded on its own
                 }
                 S.seeds.push_back(sd);
                 ++R.n_seeds;
             }
-            S.partial_elems = std::max<uint64_t>(S.partial_elems, R.total_blocks);
+            sums += R.total_blocks;
             S.rounds.push_back(R);
         }
+        S.partial_elems = std::max<uint64_t>(S.partial_elems, sums);
         L.n_rounds = (uint32_t)nr;
+        L.n_seed_tasks = (uint32_t)S.seed_tasks.size() - L.seed_task_begin;
     }
     S.partial_elems += 16;
     return S;
@@ -483,7 +486,7 @@ void enqueue_batch_metric(const BatchSchedule &s, const std::vector<const Circui
         launch_phi<R>(phis + L.phi_begin, (int)L.n_phis, st);
         for (uint32_t r = L.round_begin; r < L.round_begin + L.n_rounds; ++r) {
             // a round: the gates its seeds need first (one kernel per gate), then
-            // all its seeds in one kernel and their T in one reduction
+            // all its seeds in one kernel
             const BatchRound &rd = s.rounds[r];
             for (uint32_t k = rd.seed_begin; k < rd.seed_begin + rd.n_seeds; ++k) {
                 const BatchSeed &sd = s.seeds[k];
@@ -508,10 +511,12 @@ void enqueue_batch_metric(const BatchSchedule &s, const std::vector<const Circui
                 pos[sd.member] = members[sd.member]->rots[sd.s].pos;
             }
             if (rd.n_multi) {
-                launch_seed_multi<R>(seed_items + rd.seed_begin, (int)rd.n_multi, rd.total_blocks, d.partials, st);
-                launch_reduce_tasks(seed_tasks + rd.seed_begin, (int)rd.n_multi, d.partials, d.lraw, st);
+                launch_seed_multi<R>(seed_items + rd.seed_begin, (int)rd.n_multi, rd.total_blocks,
+                                     d.partials + 2 * (size_t)rd.sums_begin, st);
             }
         }
+        if (L.n_seed_tasks)
+            launch_reduce_tasks(seed_tasks + L.seed_task_begin, (int)L.n_seed_tasks, d.partials, d.lraw, st);
         if (events) BCHECK(hipEventRecord((*events)[2 * li], st));
         launch_sweep_pass<R>(items + L.item_begin, (int)L.n_items, L.total_tiles, passes, ops, maps, d.adj_mats,
                              d.adj_mats32, d.partials, s.m, s.rb, reg_mode, s.width, st, real_products, s.ctrl);

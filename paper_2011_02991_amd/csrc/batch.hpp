@@ -43,6 +43,7 @@ struct BatchLaunch {
     uint32_t round_begin, n_rounds;   // the launch's column seeds, in rounds
     uint32_t chain_begin, n_chains, phi_begin, n_phis;   // those of the small members
     int chain_max_n;
+    uint32_t seed_task_begin, n_seed_tasks;
 };
 
 // The column seeds of members whose register fits the chain kernel (state in
@@ -67,8 +68,8 @@ struct BatchPhi {
 
 // The column seeds before a launch go in rounds: a round holds at most one
 // seed per member (a member's seeds depend on each other through its forward
-// register), and all of a round's seeds run as one kernel (launch_seed_multi)
-// and one reduction of their T.  A seed may first need gates the seed kernel
+// register), and all of a round's seeds run as one kernel (launch_seed_multi);
+// the T of all rounds are reduced together at the end.  A seed may first need gates the seed kernel
 // does not apply (one kernel per gate, up to fwd_to).
 struct BatchSeed {
     int member;
@@ -83,6 +84,7 @@ struct BatchSeed {
 };
 struct BatchRound {
     uint32_t seed_begin, n_seeds, total_blocks;
+    uint32_t sums_begin; // where the round's work-group sums start among the launch's
     uint32_t n_multi;   // the first n_multi seeds run in the one kernel (registers of >= 3 qubits)
 };
 
@@ -106,7 +108,7 @@ struct BatchSchedule {
     std::vector<BatchChainStep> chain_steps;
     std::vector<BatchChain> chains;
     std::vector<BatchPhi> phis;
-    std::vector<ReduceTask> seed_tasks;                      // per seed: its T from the round's partials
+    std::vector<ReduceTask> seed_tasks;                      // T of the seeds run in the rounds' kernels
     std::vector<BatchLaunch> launches;
     std::vector<int> singles;                                // members with P == 1 (no columns)
     uint64_t arena_bytes = 0;

@@ -1266,6 +1266,7 @@ void launch_advance_seed(void *psi, void *lam, void *phi, int n, int qr, const d
     hipLaunchKernelGGL(k_advance_seed<R>, dim3(nb), dim3(kBlock), 0, st, (typename Cplx<R>::T *)psi,
                        (typename Cplx<R>::T *)lam, (typename Cplx<R>::T *)phi, n, qr, m_dev, qs, axis, partials);
     check_launch();
+    if (!dest) return;
     hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kBlock), 0, st, (const double *)partials, nb, dest);
     check_launch();
 }
@@ -1327,6 +1328,7 @@ void launch_advance2_seed(void *psi, void *lam, void *phi, int n, int qa, const 
     }
 #undef QNG_ADV2
     check_launch();
+    if (!dest) return;
     hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kBlock), 0, st, (const double *)partials, nb, dest);
     check_launch();
 }

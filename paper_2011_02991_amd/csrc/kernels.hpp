@@ -100,6 +100,7 @@ void launch_seed(const void *y, void *lam, void *phi, int n, int q, int axis, hi
 // psi <- R psi (R: the rotation on qubit qr whose matrix is m_dev, 8 doubles;
 // qr < 0: no gate), lam = psi, phi = sigma_qs psi (axis 0/1/2 = X/Y/Z) and
 // dest (one complex128) = <psi| sigma_qs |psi>.  partials: reduce_blocks(n) complex128.
+// (dest nullptr: the work-groups' partials, reduce_blocks(n) of them, are left for one reduction with others)
 template <typename R>
 void launch_advance_seed(void *psi, void *lam, void *phi, int n, int qr, const double *m_dev, int qs, int axis,
                          double *partials, double *dest, hipStream_t st);
