@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <map>
 #include <numeric>
 #include <string>
@@ -356,8 +357,9 @@ void upload_batch_images(const BatchSchedule &s, const BatchDevice &d, hipStream
         if (s.width > 2) it.regD = d.arena + (uintptr_t)it.regD;
         if (s.width > 3) it.regE = d.arena + (uintptr_t)it.regE;
     }
+    std::vector<char> image(L.total);   // one copy for all
     auto put = [&](size_t off, const void *src, size_t bytes) {
-        if (bytes) BCHECK(hipMemcpyAsync(d.images + off, src, bytes, hipMemcpyHostToDevice, st));
+        if (bytes) std::memcpy(image.data() + off, src, bytes);
     };
     put(L.passes, s.passes.data(), s.passes.size() * sizeof(DevPass));
     put(L.ops, s.ops.data(), s.ops.size() * sizeof(DevOp));
@@ -400,7 +402,8 @@ void upload_batch_images(const BatchSchedule &s, const BatchDevice &d, hipStream
     put(L.chain_steps, steps.data(), steps.size() * sizeof(ChainStep));
     put(L.chains, chains.data(), chains.size() * sizeof(ChainItem));
     put(L.phis, phis.data(), phis.size() * sizeof(PhiItem));
-    BCHECK(hipStreamSynchronize(st));   // the host images are released at return
+    if (!image.empty()) BCHECK(hipMemcpyAsync(d.images, image.data(), image.size(), hipMemcpyHostToDevice, st));
+    BCHECK(hipStreamSynchronize(st));   // the image is released at return
 }
 
 int batch_final_pos(const Circuit &c) { return c.P ? c.rots[c.P - 1].pos : 0; }
