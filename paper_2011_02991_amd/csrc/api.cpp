@@ -527,7 +527,8 @@ template <typename R> struct Engine {
         }
         for (; pos < c.M; ++pos) apply(pos, false, psi, nullptr);
         if (psi_copy_c128) { ++ctx->stats.other_launches; launch_to_c128<R>(psi, psi_copy_c128, n, negated, st); }
-        energy(psi, lam);
+        const bool fused = want_grad && c.P > 0 && gplan;
+        energy(psi, lam, fused);
         if (!want_grad || c.P == 0) return;
         if (gplan) {
             run_fused_gradient<R>(*gplan, c, pb.adj, lam, psi, graw(), gscratch, gscratch_bytes, st, &ctx->stats,
@@ -567,8 +568,8 @@ template <typename R> struct Engine {
     }
 
     // out = H psi and E = <psi|out> (into eraw), one pass over the register per
-    // chunk of terms
-    void energy(const void *psi, void *out) {
+    // chunk of terms (times_i: out = i H psi, what run_fused_gradient takes)
+    void energy(const void *psi, void *out, bool times_i) {
         std::vector<HamTerm> terms(pb.ham.size());
         for (size_t t = 0; t < pb.ham.size(); ++t) {
             const PauliTerm &h = pb.ham[t];
@@ -577,7 +578,7 @@ template <typename R> struct Engine {
             terms[t] = HamTerm{h.flip, h.zy, c.real(), c.imag()};
         }
         ctx->stats.other_launches += 1 + (int64_t)(terms.size() + kHamChunk - 1) / kHamChunk;
-        launch_pauli_sum<R>(psi, out, n, terms.data(), (int)terms.size(), partials(), eraw(), st);
+        launch_pauli_sum<R>(psi, out, n, terms.data(), (int)terms.size(), partials(), eraw(), st, times_i);
     }
 };
 

@@ -882,15 +882,15 @@ void run_fused_gradient(const SweepPlan &g, const Circuit &c, const std::vector<
     for (size_t t = 0; t < items.size(); ++t) {
         if (profile) FCHECK(hipEventRecord(ev[2 * t], st));
         launch_sweep_pass<R>(d_items + t, 1, tiles, d_passes, d_ops, d_maps, d_mats, d_mats32, d_partials, g.m, g.rb,
-                             reg_mode, 1, st, false, g.ctrl);
+                             reg_mode, 1, st, true, g.ctrl);
         if (profile) FCHECK(hipEventRecord(ev[2 * t + 1], st));
         const uint32_t nt = task_begin[t + 1] - task_begin[t];
-        launch_reduce_tasks(d_tasks + task_begin[t], (int)nt, d_partials, graw, st);
+        launch_reduce_tasks(d_tasks + task_begin[t], (int)nt, d_partials, graw, st, true);
         ++stats->sweep_launches;
         ++stats->other_launches;
         stats->sweep_tiles += tiles;
         stats->sweep_bytes += 4.0 * (double)V;
-        stats->sweep_flops += 20.0 * (double)nt * (double)((uint64_t)1 << c.n);
+        stats->sweep_flops += sweep_flops_per_amp(1, true) * (double)nt * (double)((uint64_t)1 << c.n);
     }
     if (profile) {
         FCHECK(hipStreamSynchronize(st));

@@ -975,7 +975,7 @@ __global__ void k_pauli_term(const typename Cplx<R>::T *psi, typename Cplx<R>::T
 // conj(psi[x]) out[x] in FP64.
 struct HamChunk {
     HamTerm t[kHamChunk];
-    int n_terms, first;
+    int n_terms, first, times_i;   // times_i: out holds i times the sum (E is of the sum itself)
 };
 
 template <typename R>
@@ -996,7 +996,12 @@ __global__ void k_pauli_sum(const typename Cplx<R>::T *psi, typename Cplx<R>::T 
             acc.x += sgn * (cr * v.x - ci * v.y);
             acc.y += sgn * (cr * v.y + ci * v.x);
         }
-        out[x] = acc;
+        C o = acc;
+        if (h.times_i) {
+            o.x = -acc.y;
+            o.y = acc.x;
+        }
+        out[x] = o;
         if (partials) {
             const C p = psi[x];
             cmac(er, ei, p.x, p.y, acc.x, acc.y);
@@ -1335,7 +1340,7 @@ void launch_advance2_seed(void *psi, void *lam, void *phi, int n, int qa, const 
 
 template <typename R>
 void launch_pauli_sum(const void *psi, void *out, int n, const HamTerm *terms, int n_terms, double *partials,
-                      double *dest, hipStream_t st) {
+                      double *dest, hipStream_t st, bool times_i) {
     const int nb = reduce_blocks(n);
     for (int t0 = 0; t0 < n_terms || t0 == 0; t0 += kHamChunk) {
         HamChunk h;
@@ -1343,6 +1348,7 @@ void launch_pauli_sum(const void *psi, void *out, int n, const HamTerm *terms, i
         h.first = t0 == 0;
         for (int k = 0; k < h.n_terms; ++k) h.t[k] = terms[t0 + k];
         const bool last = t0 + kHamChunk >= n_terms;
+        h.times_i = last && times_i;
         hipLaunchKernelGGL(k_pauli_sum<R>, dim3(nb), dim3(kBlock), 0, st, (const typename Cplx<R>::T *)psi,
                            (typename Cplx<R>::T *)out, n, h, (last && dest) ? partials : nullptr);
         check_launch();
@@ -1423,7 +1429,8 @@ void launch_grad_from_raw(const double *graw, const int *param_of, int P, double
                                          double *, hipStream_t);                                                  \
     template void launch_seed_multi<R>(const SeedItem *, int, uint32_t, double *, hipStream_t);                      \
     template void launch_pauli_term<R>(const void *, void *, int, uint64_t, uint64_t, int, double, int, hipStream_t); \
-    template void launch_pauli_sum<R>(const void *, void *, int, const HamTerm *, int, double *, double *, hipStream_t); \
+    template void launch_pauli_sum<R>(const void *, void *, int, const HamTerm *, int, double *, double *, hipStream_t, \
+                                         bool);                                                                \
     template void launch_chain<R>(const ChainItem *, int, int, hipStream_t);                                       \
     template void launch_phi<R>(const PhiItem *, int, hipStream_t);                                                \
     template void launch_advance2_seed<R>(void *, void *, void *, int, int, const double *, int, const double *, int, \

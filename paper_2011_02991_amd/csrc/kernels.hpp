@@ -173,7 +173,7 @@ struct HamTerm {
 };
 template <typename R>
 void launch_pauli_sum(const void *psi, void *out, int n, const HamTerm *terms, int n_terms, double *partials,
-                      double *dest, hipStream_t st);
+                      double *dest, hipStream_t st, bool times_i = false);
 
 // out (+)= coeff * (-i)^{n_y} (-1)^{popcount(x & zy)} psi[x ^ flip]; first != 0 overwrites.
 template <typename R>

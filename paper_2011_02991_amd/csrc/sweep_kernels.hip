@@ -22,7 +22,8 @@
 //  * Diagonal operations (RZ, CZ, Z inner products) act on any bit: its value
 //    comes from the register index, the thread index or the tile base.
 //  * Between phases the tile is exchanged through LDS (one register at a time)
-//    to the next mapping, the only place where barriers are needed.
+//    to the next mapping, the only place where barriers are needed (not where
+//    the exchange stays within each wavefront).
 //  * Inner products: each thread's share (register precision, then FP64) is
 //    summed within each 16-lane row with DPP exchanges and across the
 //    wavefront's rows with two lane exchanges, kept per (slot, wavefront) in
@@ -1282,7 +1283,7 @@ __device__ __forceinline__ void seed_handler(Regs<CT, T, W> &x, const OpD &op, i
     }
 }
 
-// Occupancy target: three waves per SIMD (the 53 KB of LDS of a work-group
+// Occupancy target: three waves per SIMD (the 51 KB of LDS of a work-group
 // allow three per CU).  The 16-amplitude kernel with one phi register reaches
 // it by itself (114 VGPRs; 158 with every product in FP64) and gets no bound;
 // with two phi registers it is held to 168 VGPRs (it needs 146; with every
@@ -1590,7 +1591,7 @@ constexpr int kReduceThreads = 1024;
 
 __global__ __launch_bounds__(kReduceThreads) void k_reduce_tasks(const ReduceTask *__restrict__ tasks,
                                                                  const double2 *__restrict__ partials,
-                                                                 double2 *__restrict__ results) {
+                                                                 double2 *__restrict__ results, int imag) {
     __shared__ double sr[kReduceThreads], si[kReduceThreads];
     const ReduceTask t = tasks[blockIdx.x];
     const double2 *p = partials + t.off;
@@ -1619,7 +1620,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_tasks(const ReduceTas
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) results[t.dest] = make_double2(sr[0], si[0]);
+    if (threadIdx.x == 0) results[t.dest] = imag ? make_double2(-si[0], sr[0]) : make_double2(sr[0], si[0]);
 }
 
 template <typename CT> size_t smem_bytes(int m) {
@@ -1820,10 +1821,10 @@ void launch_sweep_pass(const LaunchItem *items, int n_items, uint32_t total_tile
 }
 
 void launch_reduce_tasks(const ReduceTask *tasks, int n_tasks, const double *partials, double *results,
-                         hipStream_t st) {
+                         hipStream_t st, bool imag) {
     if (n_tasks <= 0) return;
     hipLaunchKernelGGL(k_reduce_tasks, dim3(n_tasks), dim3(kReduceThreads), 0, st, tasks,
-                       (const double2 *)partials, (double2 *)results);
+                       (const double2 *)partials, (double2 *)results, imag ? 1 : 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) throw e;
 }
