@@ -152,6 +152,7 @@ BatchSchedule build_batch_schedule(const std::vector<const Circuit *> &members,
             it.tile_begin = L.total_tiles;
             it.pass = (uint32_t)(pass_base[a.b] + p.col_pass_begin[a.col] + (int64_t)a.t);
             it.ntiles = tiles;
+            L.max_tiles = std::max(L.max_tiles, tiles);
             it.partial_off = poff;
             const uint64_t V = (uint64_t(1) << n) * (uint64_t)amp;
             it.regA = (void *)(uintptr_t)a.reg;
@@ -324,6 +325,7 @@ BatchSchedule build_batch_schedule(const std::vector<const Circuit *> &members,
                     const uint64_t groups = uint64_t(1) << (c.n - 3);
                     sd.nblocks = (uint32_t)std::min<uint64_t>(kSeedBlocksMax, (groups + 255) / 256);
                     sd.block_begin = R.total_blocks;
+                    L.max_sums = std::max(L.max_sums, sd.nblocks);
                     R.total_blocks += sd.nblocks;
                     S.seed_tasks.push_back(ReduceTask{(uint64_t)sums + sd.block_begin, sd.nblocks,
                                                       (int32_t)(S.lraw_base[pr.member] + (int64_t)c.P * c.P + sidx)});
@@ -519,12 +521,12 @@ void enqueue_batch_metric(const BatchSchedule &s, const std::vector<const Circui
             }
         }
         if (L.n_seed_tasks)
-            launch_reduce_tasks(seed_tasks + L.seed_task_begin, (int)L.n_seed_tasks, d.partials, d.lraw, st);
+            launch_reduce_tasks(seed_tasks + L.seed_task_begin, (int)L.n_seed_tasks, L.max_sums, d.partials, d.lraw, st);
         if (events) BCHECK(hipEventRecord((*events)[2 * li], st));
         launch_sweep_pass<R>(items + L.item_begin, (int)L.n_items, L.total_tiles, passes, ops, maps, d.adj_mats,
                              d.adj_mats32, d.partials, s.m, s.rb, reg_mode, s.width, st, real_products, s.ctrl);
         if (events) BCHECK(hipEventRecord((*events)[2 * li + 1], st));
-        launch_reduce_tasks(tasks + L.task_begin, (int)L.n_tasks, d.partials, d.lraw, st);
+        launch_reduce_tasks(tasks + L.task_begin, (int)L.n_tasks, L.max_tiles, d.partials, d.lraw, st);
     }
 }
 

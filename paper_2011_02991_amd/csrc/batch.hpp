@@ -43,6 +43,7 @@ struct BatchLaunch {
     uint32_t round_begin, n_rounds;   // the launch's column seeds, in rounds
     uint32_t chain_begin, n_chains, phi_begin, n_phis;   // those of the small members
     int chain_max_n;
+    uint32_t max_tiles, max_sums;     // largest counts among the launch's reduce tasks and its seeds'
     uint32_t seed_task_begin, n_seed_tasks;
 };
 

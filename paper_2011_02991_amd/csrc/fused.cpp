@@ -559,7 +559,7 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
             at_seg = seg_next;
         }
         if (G.n_seeds) {
-            launch_reduce_tasks(d_tasks + G.seed_begin, (int)G.n_seeds, d_partials, buf.traw, st);
+            launch_reduce_tasks(d_tasks + G.seed_begin, (int)G.n_seeds, (uint32_t)nb, d_partials, buf.traw, st);
             ++stats->other_launches;
         }
         for (size_t li = G.launch_begin; li < G.launch_end; ++li) {
@@ -582,7 +582,7 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
                 stats->sweep_flops += (6.0 + 6.0 / W) * (double)L.n_tasks * (double)((uint64_t)1 << n);
                 continue;
             }
-            launch_reduce_tasks(d_tasks + L.task_begin, (int)L.n_tasks, d_partials, buf.lraw, st);
+            launch_reduce_tasks(d_tasks + L.task_begin, (int)L.n_tasks, tiles, d_partials, buf.lraw, st);
             ++stats->other_launches;
             stats->sweep_flops +=
                 sweep_flops_per_amp(W, real_products) * (double)L.n_tasks * (double)((uint64_t)1 << n);
@@ -885,7 +885,7 @@ void run_fused_gradient(const SweepPlan &g, const Circuit &c, const std::vector<
                              reg_mode, 1, st, true, g.ctrl);
         if (profile) FCHECK(hipEventRecord(ev[2 * t + 1], st));
         const uint32_t nt = task_begin[t + 1] - task_begin[t];
-        launch_reduce_tasks(d_tasks + task_begin[t], (int)nt, d_partials, graw, st, true);
+        launch_reduce_tasks(d_tasks + task_begin[t], (int)nt, tiles, d_partials, graw, st, true);
         ++stats->sweep_launches;
         ++stats->other_launches;
         stats->sweep_tiles += tiles;

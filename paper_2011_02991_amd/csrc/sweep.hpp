@@ -372,10 +372,11 @@ void launch_sweep_pass_exact(const LaunchItem *items, int n_items, uint32_t tota
 void launch_sweep_pass_real_exact(const LaunchItem *items, int n_items, uint32_t total_tiles,
                                   const DevPass *passes, const DevOp *ops, const DevMap *maps, const float *mats32,
                                   double *partials, int m, int rb, int width, hipStream_t st, bool ctrl);
+// max_count: the largest count among the tasks.
 // imag: the partials' sums s are written as i s (parts of products taken as their
 // imaginary parts).
-void launch_reduce_tasks(const ReduceTask *tasks, int n_tasks, const double *partials, double *results,
-                         hipStream_t st, bool imag = false);
+void launch_reduce_tasks(const ReduceTask *tasks, int n_tasks, uint32_t max_count, const double *partials,
+                         double *results, hipStream_t st, bool imag = false);
 // The passes without inner products (sweep_kernels_states.hip): lambda and
 // the phi registers go through the adjoint gates and the in-pass seeds only.
 // width 0: lambda alone (the forward plans: the table then holds the shears

@@ -41,3 +41,21 @@ def test_exchanges(env, tile, block, prec):
         err = np.abs(res[key] - want[key]).max() / scale
         print(tile, block, prec, key, err, "tol", tol, flush=True)
         assert err <= tol
+
+
+@pytest.mark.parametrize("n", [15, 16, 17])
+def test_tile_sums(env, n):
+    """Sums over 128, 256 and 512 tiles (one wavefront up to 256, then 1024
+    threads)."""
+    q, ctx = env
+    pr = W.random_circuit(n, 14, 9350 + n, n_terms=3)
+    want = oracle.step(pr)
+    ctx.set_option(q.OPT_TILE_QUBITS, 8)
+    try:
+        res = ctx.step(q.Circuit.from_problem(pr), pr.theta, pr.dt, pr.tikhonov)
+    finally:
+        ctx.set_option(q.OPT_TILE_QUBITS, 0)
+    for key, scale in (("G", np.abs(want["G"]).max()), ("grad", np.abs(pr.coeff).sum())):
+        err = np.abs(res[key] - want[key]).max() / scale
+        print(n, key, err, flush=True)
+        assert err <= 1e-10
