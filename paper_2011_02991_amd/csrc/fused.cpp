@@ -76,14 +76,17 @@ bool use_chain(int n, size_t amp_bytes) { return n <= chain_qubits(amp_bytes); }
 
 size_t fused_scratch_bytes(const SweepPlan &plan, const FusedRun &fr, int M) {
     size_t b = 0;
+    // the chain's images, in place of the negated matrices and the forward plan's
+    size_t chain = 0;
     if (plan.n <= chain_qubits(8)) {
-        b += align256((size_t)(2 * M + 2 * plan.P + 8) * sizeof(ChainStep) + 64);   // a gate and a DOT each at most
-        b += align256((plan.cols.size() + 1) * (sizeof(ChainItem) + sizeof(PhiItem)) + 128);
+        chain += align256((size_t)(M + (plan.ctrl ? plan.P : 0) + 2) * sizeof(ChainStep) + 64);
+        chain += align256((plan.cols.size() + 1) * sizeof(ChainItem) + 64);
+        chain += align256(plan.cols.size() * sizeof(PhiItem) + 64);
     }
     b += align256((size_t)M * 64 + 64);                                  // matrix table (FP64)
     b += align256((size_t)M * 32 + 64);                                  // matrix table (FP32)
     b += align256((size_t)M * 64 + 64);                                  // forward matrices (FP64)
-    b += align256((size_t)(M + 1) * 64 + 64);                            // the same negated, and -I
+    size_t forward = align256((size_t)(M + 1) * 64 + 64);                // the same negated, and -I
     b += align256(plan.dev_passes.size() * sizeof(DevPass) + 64);       // passes
     b += align256(plan.dev_ops.size() * sizeof(DevOp) + 64);            // ops
     b += align256(plan.dev_maps.size() * sizeof(DevMap) + 64);          // thread mappings
@@ -92,13 +95,14 @@ size_t fused_scratch_bytes(const SweepPlan &plan, const FusedRun &fr, int M) {
     b += align256((size_t)plan.P + 1 + 64);                              // signs (derivative-state variant)
     if (plan.forward) {
         const SweepPlan &fp = *plan.forward;
-        b += align256((size_t)M * 64 + 64);                              // the gates' own shears (FP64)
-        b += align256((size_t)M * 32 + 64);                              // (FP32)
-        b += align256(fp.dev_passes.size() * sizeof(DevPass) + 64);
-        b += align256(fp.dev_ops.size() * sizeof(DevOp) + 64);
-        b += align256(fp.dev_maps.size() * sizeof(DevMap) + 64);
-        b += align256(fp.dev_passes.size() * sizeof(LaunchItem) + 64);
+        forward += align256((size_t)M * 64 + 64);                              // the gates' own shears (FP64)
+        forward += align256((size_t)M * 32 + 64);                              // (FP32)
+        forward += align256(fp.dev_passes.size() * sizeof(DevPass) + 64);
+        forward += align256(fp.dev_ops.size() * sizeof(DevOp) + 64);
+        forward += align256(fp.dev_maps.size() * sizeof(DevMap) + 64);
+        forward += align256(fp.dev_passes.size() * sizeof(LaunchItem) + 64);
     }
+    b += std::max(chain, forward);
     b += align256(fr.partial_elems * 16);
     return b;
 }
@@ -234,8 +238,8 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
     for (size_t k = 0; k < fmats.size(); ++k) nfmats[k] = -fmats[k];
     nfmats[fmats.size()] = -1.0;
     nfmats[fmats.size() + 6] = -1.0;
-    double *d_nfmats = (double *)take(nfmats.size() * 8);
-    const double *d_negI = d_nfmats + fmats.size();
+    double *d_nfmats = chain ? nullptr : (double *)take(nfmats.size() * 8);
+    const double *d_negI = chain ? nullptr : d_nfmats + fmats.size();
     DevPass *d_passes = (DevPass *)take(plan.dev_passes.size() * sizeof(DevPass));
     DevOp *d_ops = (DevOp *)take(plan.dev_ops.size() * sizeof(DevOp));
     DevMap *d_maps = (DevMap *)take(plan.dev_maps.size() * sizeof(DevMap));
@@ -353,7 +357,7 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
     up.put(d_mats, mats);
     up.put(d_mats32, mats32);
     up.put(d_fmats, fmats);
-    up.put(d_nfmats, nfmats);
+    if (!chain) up.put(d_nfmats, nfmats);
     up.put(d_passes, plan.dev_passes);
     up.put(d_ops, plan.dev_ops);
     up.put(d_maps, plan.dev_maps);
