@@ -669,7 +669,8 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
     if (states && (!fused || !pb.rot_block.empty()))
         fail(QNG_E_UNSUPPORTED, "the derivative-state variant takes the fused passes (no Pauli string without a "
                                 "letter) and the full metric");
-    const SweepPlan *plan = nullptr;
+    // held through the call: the look-ups of the other plans below may evict it
+    std::shared_ptr<const SweepPlan> plan;
     FusedRun fr;
     size_t scratch = 0, gram_bytes = 0;
     int chunk_cols = 0;
@@ -679,8 +680,8 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
         const bool f64_regs = amp == 16 || ctx->opt_f64_regs;
         const bool blocked = !pb.rot_block.empty();
         const int width = blocked ? 1 : block_width(ctx->opt_block, c, ctx->opt_tile, (int)amp, f64_regs);
-        plan = &ctx->sweep_cache.get(c, plan_tile(width, ctx->opt_tile), (int)amp, ctx->opt_small, f64_regs, width,
-                                     blocked ? &pb.rot_block : nullptr);
+        plan = ctx->sweep_cache.get_shared(c, plan_tile(width, ctx->opt_tile), (int)amp, ctx->opt_small, f64_regs,
+                                           width, blocked ? &pb.rot_block : nullptr);
         size_t free_b = 0, total_b = 0;
         HIPCHECK(hipMemGetInfo(&free_b, &total_b));
         const size_t avail = free_b + ctx->ws_bytes;

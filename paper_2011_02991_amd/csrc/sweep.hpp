@@ -277,14 +277,10 @@ SweepPlan build_gradient_plan(const Circuit &c, int tile_qubits, int amp_bytes, 
 // plan of width 0 with one column; its gate table holds the gates themselves).
 SweepPlan build_apply_plan(const Circuit &c, int from, int tile_qubits, int amp_bytes);
 
+// Plans by circuit structure.  Every look-up hands out an owning pointer and may
+// evict any other plan: a caller holds what it looked up for as long as it uses it.
 struct SweepCache {
     std::map<std::vector<int32_t>, std::shared_ptr<SweepPlan>> plans;
-    const SweepPlan &get(const Circuit &c, int tile_qubits, int amp_bytes, int small, bool reg_f64, int width = 1,
-                         const std::vector<int> *rot_block = nullptr) {
-        return *get_shared(c, tile_qubits, amp_bytes, small, reg_f64, width, rot_block);
-    }
-    // The plan stays alive while the caller holds the pointer, even if the
-    // cache evicts it.
     std::shared_ptr<const SweepPlan> get_shared(const Circuit &c, int tile_qubits, int amp_bytes, int small,
                                                 bool reg_f64, int width = 1,
                                                 const std::vector<int> *rot_block = nullptr);
