@@ -908,6 +908,21 @@ void append_structure_key(const Circuit &c, std::vector<int32_t> &key) {
     }
 }
 
+template <typename F>
+std::shared_ptr<const SweepPlan> SweepCache::look_up(const std::vector<int32_t> &key, F build) {
+    auto it = plans.find(key);
+    if (it == plans.end()) {
+        auto plan = std::make_shared<SweepPlan>(build());
+        if (plans.size() >= kMaxPlans)
+            plans.erase(std::min_element(plans.begin(), plans.end(), [](const auto &a, const auto &b) {
+                return a.second.used < b.second.used;
+            }));
+        it = plans.emplace(key, Entry{std::move(plan), 0}).first;
+    }
+    it->second.used = ++look_ups;
+    return it->second.plan;
+}
+
 std::shared_ptr<const SweepPlan> SweepCache::get_shared(const Circuit &c, int tile_qubits, int amp_bytes, int small,
                                                         bool reg_f64, int width, const std::vector<int> *rot_block) {
     std::vector<int32_t> key = {tile_qubits, amp_bytes, small, reg_f64 ? 1 : 0, width};
@@ -916,35 +931,20 @@ std::shared_ptr<const SweepPlan> SweepCache::get_shared(const Circuit &c, int ti
         key.insert(key.end(), rot_block->begin(), rot_block->end());
     }
     append_structure_key(c, key);
-    auto it = plans.find(key);
-    if (it != plans.end()) return it->second;
-    if (plans.size() >= 256) plans.clear();
-    auto p = std::make_shared<SweepPlan>(build_sweep_plan(c, tile_qubits, amp_bytes, small, reg_f64, width, rot_block));
-    plans[key] = p;
-    return p;
+    return look_up(key, [&] { return build_sweep_plan(c, tile_qubits, amp_bytes, small, reg_f64, width, rot_block); });
 }
 
 std::shared_ptr<const SweepPlan> SweepCache::get_gradient(const Circuit &c, int tile_qubits, int amp_bytes,
                                                           bool reg_f64) {
     std::vector<int32_t> key = {-1, tile_qubits, amp_bytes, reg_f64 ? 1 : 0};
     append_structure_key(c, key);
-    auto it = plans.find(key);
-    if (it != plans.end()) return it->second;
-    if (plans.size() >= 256) plans.clear();
-    auto p = std::make_shared<SweepPlan>(build_gradient_plan(c, tile_qubits, amp_bytes, reg_f64));
-    plans[key] = p;
-    return p;
+    return look_up(key, [&] { return build_gradient_plan(c, tile_qubits, amp_bytes, reg_f64); });
 }
 
 std::shared_ptr<const SweepPlan> SweepCache::get_apply(const Circuit &c, int from, int tile_qubits, int amp_bytes) {
     std::vector<int32_t> key = {-3, from, tile_qubits, amp_bytes};
     append_structure_key(c, key);
-    auto it = plans.find(key);
-    if (it != plans.end()) return it->second;
-    if (plans.size() >= 256) plans.clear();
-    auto p = std::make_shared<SweepPlan>(build_apply_plan(c, from, tile_qubits, amp_bytes));
-    plans[key] = p;
-    return p;
+    return look_up(key, [&] { return build_apply_plan(c, from, tile_qubits, amp_bytes); });
 }
 
 FusedRun fused_config(const SweepPlan &plan, int requested_streams, size_t state_bytes, size_t free_bytes) {

@@ -279,13 +279,25 @@ SweepPlan build_apply_plan(const Circuit &c, int from, int tile_qubits, int amp_
 
 // Plans by circuit structure.  Every look-up hands out an owning pointer and may
 // evict any other plan: a caller holds what it looked up for as long as it uses it.
+// A new plan takes the place of the one not looked up for the longest time.  A
+// step has three plans (metric, gradient, forward pass) and planning it again costs
+// more than running it, so a program that goes round up to 128 circuits keeps all.
 struct SweepCache {
-    std::map<std::vector<int32_t>, std::shared_ptr<SweepPlan>> plans;
+    static constexpr size_t kMaxPlans = 3 * 128;
+    struct Entry {
+        std::shared_ptr<SweepPlan> plan;
+        uint64_t used;   // number of the last look-up that returned it
+    };
+    std::map<std::vector<int32_t>, Entry> plans;
+    uint64_t look_ups = 0;
     std::shared_ptr<const SweepPlan> get_shared(const Circuit &c, int tile_qubits, int amp_bytes, int small,
                                                 bool reg_f64, int width = 1,
                                                 const std::vector<int> *rot_block = nullptr);
     std::shared_ptr<const SweepPlan> get_gradient(const Circuit &c, int tile_qubits, int amp_bytes, bool reg_f64);
     std::shared_ptr<const SweepPlan> get_apply(const Circuit &c, int from, int tile_qubits, int amp_bytes);
+
+  private:
+    template <typename F> std::shared_ptr<const SweepPlan> look_up(const std::vector<int32_t> &key, F build);
 };
 
 // Structure key of a circuit (gate kinds, qubits, which gates are rotations).

@@ -1,7 +1,11 @@
-// The look-ups of a step, in its order (metric, gradient, forward pass), over
-// more distinct circuits than the cache keeps; built with AddressSanitizer by
-// test_plan_cache.py.  Prints "ok".
+// The look-ups of a step, in its order (metric, gradient, forward pass); built
+// with AddressSanitizer by test_plan_cache.py, which names one of the checks:
+//   use    the plans of 400 distinct circuits, each read after its last look-up
+//   round  128 circuits over and over: no plan is built twice
+//   oldest one circuit more evicts the plans not looked up for the longest time
+// Prints "ok".
 #include <cstdio>
+#include <cstring>
 #include <type_traits>
 #include <utility>
 
@@ -34,18 +38,66 @@ static_assert(!decltype(borrows<SweepCache>(0))::value, "a look-up returns a pla
 
 }  // namespace
 
-int main() {
+namespace {
+
+struct Plans {
+    std::shared_ptr<const SweepPlan> metric, gradient, apply;
+};
+
+Plans look_up(SweepCache &cache, int k) {
+    const Circuit c = circuit(k);
+    Plans p;
+    p.metric = cache.get_shared(c, 0, 16, 1, true, 2);
+    p.gradient = cache.get_gradient(c, 0, 16, true);
+    p.apply = cache.get_apply(c, c.rots[c.P - 1].pos, 0, 16);
+    return p;
+}
+
+bool use() {
     SweepCache cache;
     long ops = 0;
     for (int k = 0; k < 400; ++k) {
-        const Circuit c = circuit(k);
-        const auto plan = cache.get_shared(c, 0, 16, 1, true, 2);
-        const auto gradient = cache.get_gradient(c, 0, 16, true);
-        const auto apply = cache.get_apply(c, c.rots[c.P - 1].pos, 0, 16);
-        for (const auto &p : {plan, gradient, apply})
-            for (const DevOp &op : p->dev_ops) ops += op.type;
+        const Plans p = look_up(cache, k);
+        for (const auto &plan : {p.metric, p.gradient, p.apply})
+            for (const DevOp &op : plan->dev_ops) ops += op.type;
     }
-    if (ops <= 0) return 1;
-    std::puts("ok");
-    return 0;
+    return ops > 0;
+}
+
+bool round() {
+    SweepCache cache;
+    std::vector<Plans> first;
+    for (int k = 0; k < 128; ++k) first.push_back(look_up(cache, k));
+    for (int pass = 0; pass < 2; ++pass)
+        for (int k = 0; k < 128; ++k) {
+            const Plans p = look_up(cache, k);
+            if (p.metric != first[k].metric || p.gradient != first[k].gradient || p.apply != first[k].apply) return false;
+        }
+    return true;
+}
+
+bool oldest() {
+    SweepCache cache;
+    std::vector<Plans> first;
+    for (int k = 0; k < 128; ++k) first.push_back(look_up(cache, k));
+    look_up(cache, 0);     // now circuit 1 is the one not seen for the longest time
+    look_up(cache, 128);
+    if (cache.plans.size() > 384) return false;
+    for (int k = 0; k < 128; ++k) {
+        if (k == 1) continue;
+        if (look_up(cache, k).metric != first[k].metric) return false;
+    }
+    return look_up(cache, 1).metric != first[1].metric;
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    const char *check = argc > 1 ? argv[1] : "";
+    const bool ok = !std::strcmp(check, "use")      ? use()
+                    : !std::strcmp(check, "round")  ? round()
+                    : !std::strcmp(check, "oldest") ? oldest()
+                                                    : false;
+    std::puts(ok ? "ok" : "failed");
+    return ok ? 0 : 1;
 }

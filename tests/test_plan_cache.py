@@ -1,5 +1,6 @@
-"""The cache of sweep plans on the host: a plan in use outlives its eviction
-(AddressSanitizer build of the planner, look-ups in the order of a step)."""
+"""The cache of sweep plans on the host (AddressSanitizer build of the planner,
+look-ups in the order of a step): a plan in use outlives its eviction, 128
+circuits keep their plans, and one more evicts those not used for the longest time."""
 import os
 import subprocess
 
@@ -18,6 +19,7 @@ def program(tmp_path_factory):
     return exe
 
 
-def test_plans_in_use_outlive_their_eviction(program):
-    r = subprocess.run([program], capture_output=True, text=True, timeout=300)
+@pytest.mark.parametrize("check", ["use", "round", "oldest"])
+def test_plan_cache(program, check):
+    r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.split()[-1] == "ok", r.stdout + r.stderr
