@@ -724,12 +724,12 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
     }
     // the forward pass to psi (after a metric: the gates behind its last
     // rotation) in tile passes where that saves launches, i.e. passes over the
-    // register
+    // register, and the tile width asked for can hold them
     std::shared_ptr<const SweepPlan> aplan;
     const int aplan_from = spec.metric && c.P ? c.rots[c.P - 1].pos : 0;
     const size_t scratch_without_apply = scratch;
     if (ctx->opt_fusion != 0 && !c.has_strings && !spec.psi_final_dev && (spec.grad || spec.psi_out_dev) &&
-        c.M - aplan_from >= kMinFusedApply) {
+        c.M - aplan_from >= kMinFusedApply && apply_plan_fits(n, ctx->opt_tile, (int)amp)) {
         aplan = ctx->sweep_cache.get_apply(c, aplan_from, ctx->opt_tile, (int)amp);
         scratch = std::max(scratch, fused_apply_scratch_bytes(*aplan, c.M));
     }

@@ -277,6 +277,9 @@ SweepPlan build_gradient_plan(const Circuit &c, int tile_qubits, int amp_bytes, 
 // plan of width 0 with one column; its gate table holds the gates themselves).
 SweepPlan build_apply_plan(const Circuit &c, int from, int tile_qubits, int amp_bytes);
 
+// Whether tiles of the given width (0: the default) can hold such a plan.
+bool apply_plan_fits(int n, int tile_qubits, int amp_bytes);
+
 // Plans by circuit structure.  Every look-up hands out an owning pointer and may
 // evict any other plan: a caller holds what it looked up for as long as it uses it.
 // A new plan takes the place of the one not looked up for the longest time.  A

@@ -3,6 +3,8 @@
 //   use    the plans of 400 distinct circuits, each read after its last look-up
 //   round  128 circuits over and over: no plan is built twice
 //   oldest one circuit more evicts the plans not looked up for the longest time
+//   tiles  apply_plan_fits says for every register and tile width whether a plan
+//          of the forward pass can be built
 // Prints "ok".
 #include <cstdio>
 #include <cstring>
@@ -90,6 +92,32 @@ bool oldest() {
     return look_up(cache, 1).metric != first[1].metric;
 }
 
+bool tiles() {
+    for (int n = 2; n <= 33; ++n) {
+        std::vector<qng_gate> g;
+        for (int q = 0; q < 8; ++q) g.push_back({QNG_CNOT, q % n, (q + 1) % n, -1});
+        qng_circuit qc{};
+        qc.n_qubits = n;
+        qc.n_gates = (int)g.size();
+        qc.gates = g.data();
+        const Circuit c = compile_circuit(&qc);
+        for (int tile = 0; tile <= 14; ++tile)
+            for (int amp : {8, 16}) {
+                bool built = true;
+                try {
+                    build_apply_plan(c, 0, tile, amp);
+                } catch (const Error &) {
+                    built = false;
+                }
+                if (built != apply_plan_fits(n, tile, amp)) {
+                    std::printf("n %d tile %d amp %d\n", n, tile, amp);
+                    return false;
+                }
+            }
+    }
+    return true;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -97,6 +125,7 @@ int main(int argc, char **argv) {
     const bool ok = !std::strcmp(check, "use")      ? use()
                     : !std::strcmp(check, "round")  ? round()
                     : !std::strcmp(check, "oldest") ? oldest()
+                    : !std::strcmp(check, "tiles")  ? tiles()
                                                     : false;
     std::puts(ok ? "ok" : "failed");
     return ok ? 0 : 1;

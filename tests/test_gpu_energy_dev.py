@@ -1,0 +1,69 @@
+"""qng_energy_dev in the situations in which it cannot run as tile passes."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+U = {"c128": 2.0 ** -53, "c64": 2.0 ** -24}
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    import paper_2011_02991_amd as q
+    c = q.Context(0)
+    c.set_stream(None)
+    yield q, c, torch
+    c.close()
+
+
+def tolerance(pr, prec):
+    """A gate rounds an amplitude by a few units u, M of them like a random walk."""
+    return 8.0 * np.sqrt(4 * pr.n_gates) * U[prec]
+
+
+def check(env, pr, prec, E, psi):
+    want, e0 = oracle.forward(pr), oracle.energy(pr)
+    tol = tolerance(pr, prec)
+    err = np.abs(psi.cpu().numpy() - want).max() / np.abs(want).max()
+    print(pr.name, prec, "psi", err, "tol", tol, flush=True)
+    assert err <= tol and abs(float(E) - e0) <= tol * np.abs(pr.coeff).sum()
+
+
+def outputs(torch, n):
+    return (torch.zeros((), dtype=torch.float64, device="cuda"),
+            torch.zeros(2 ** n, dtype=torch.complex128, device="cuda"))
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("tile", [1, 2, 3, 4, 5, 6])
+def test_tile_too_small_for_a_plan(env, tile, prec):
+    """Tiles that leave fewer than two qubits beside the carriers hold no plan;
+    the energy needs none (with and without rotations)."""
+    q, ctx, torch = env
+    fixed = W.random_circuit(9, 30, 9801, n_terms=4)
+    gates = [g for g in fixed.gates if g[3] < 0] * 4
+    fixed = W.Problem("fixed", 9, np.asarray(gates), np.zeros(0), fixed.pauli, fixed.coeff)
+    assert len(gates) >= 8
+    ctx.set_option(q.OPT_TILE_QUBITS, tile)
+    try:
+        for pr in (W.random_circuit(9, 40, 9800, n_terms=4), fixed):
+            pr.in_state = W.random_state(9, 92)
+            ins = torch.tensor(pr.in_state, device="cuda")
+            E, psi = outputs(torch, 9)
+            circ = q.Circuit.from_problem(pr)
+            ctx.energy_dev(circ, pr.theta, E.data_ptr(), psi.data_ptr(), in_state_dev_ptr=ins.data_ptr(), prec=prec)
+            torch.cuda.synchronize()
+            check(env, pr, prec, E, psi)
+            if not len(pr.theta):
+                E.zero_()
+                grad = torch.zeros(1, dtype=torch.float64, device="cuda")
+                ctx.energy_grad_dev(circ, pr.theta, E.data_ptr(), grad.data_ptr(), in_state_dev_ptr=ins.data_ptr(),
+                                    prec=prec)
+                torch.cuda.synchronize()
+                check(env, pr, prec, E, psi)
+    finally:
+        ctx.set_option(q.OPT_TILE_QUBITS, 0)
