@@ -81,6 +81,7 @@ struct qng_ctx {
     char *fixed_ws = nullptr;
     size_t fixed_ws_bytes = 0;
     SweepCache sweep_cache;
+    Staging staging;
     std::map<std::vector<int32_t>, std::shared_ptr<BatchClass>> batch_classes;
     std::map<std::vector<int32_t>, BatchTuning> tuned;
 };
@@ -339,6 +340,7 @@ template <typename R> struct Engine {
     // shares the gradient's scratch, which is free until the reverse sweep
     const SweepPlan *aplan = nullptr;
     int aplan_from = 0;
+    Staging *staging = nullptr;   // for the plan's images (nullptr: wait for their copy)
     int reg_mode = REG_F32;
     bool stepped = false;     // one kernel per sweep step (circuits the fused passes do not take)
 
@@ -522,7 +524,8 @@ template <typename R> struct Engine {
         void *psi = state(0), *lam = state(1);
         bool negated = false;
         if (aplan && pos == aplan_from) {
-            negated = run_fused_apply<R>(*aplan, c, pb.fwd, pos, psi, gscratch, gscratch_bytes, st, &ctx->stats);
+            negated = run_fused_apply<R>(*aplan, c, pb.fwd, pos, psi, gscratch, gscratch_bytes, staging, st,
+                                         &ctx->stats);
             pos = c.M;
         }
         for (; pos < c.M; ++pos) apply(pos, false, psi, nullptr);
@@ -647,6 +650,14 @@ void unpack_to_params(const Problem &pb, const double *lraw, const double *traw,
 // step gate by gate, 931 us in one pass; below 8 the launches win).
 constexpr int kMinFusedApply = 8;
 
+// Whether the stream is being captured (or cannot be asked because another is).
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 struct CallResult {
     // device pointers into the workspace
     double *G = nullptr, *T = nullptr, *graw = nullptr, *eraw = nullptr;
@@ -728,7 +739,10 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
     std::shared_ptr<const SweepPlan> aplan;
     const int aplan_from = spec.metric && c.P ? c.rots[c.P - 1].pos : 0;
     const size_t scratch_without_apply = scratch;
-    if (ctx->opt_fusion != 0 && !c.has_strings && !spec.psi_final_dev && (spec.grad || spec.psi_out_dev) &&
+    // the energy alone does not wait for its stream, and can be captured: its gate
+    // kernels carry their matrices as arguments, which a replay finds unchanged
+    const bool energy_only = spec.psi_out_dev && !spec.grad && !spec.metric;
+    if (ctx->opt_fusion != 0 && !(energy_only && capturing(ctx->stream)) && !c.has_strings && !spec.psi_final_dev && (spec.grad || spec.psi_out_dev) &&
         c.M - aplan_from >= kMinFusedApply && apply_plan_fits(n, ctx->opt_tile, (int)amp)) {
         aplan = ctx->sweep_cache.get_apply(c, aplan_from, ctx->opt_tile, (int)amp);
         scratch = std::max(scratch, fused_apply_scratch_bytes(*aplan, c.M));
@@ -775,6 +789,7 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
     }
     e.aplan = aplan.get();
     e.aplan_from = aplan_from;
+    if (energy_only) e.staging = &ctx->staging;
     e.gscratch = base + L.sweep;
     e.gscratch_bytes = L.sweep_bytes;
     e.stepped = stepped;
@@ -784,7 +799,7 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
         HIPCHECK(hipMemcpyAsync(base + L.staging, spec.in_host, (size_t(1) << n) * 16, hipMemcpyHostToDevice, st));
         in_c128 = base + L.staging;
     }
-    if (c.P)
+    if (c.P && !energy_only)
         HIPCHECK(hipMemcpyAsync(base + L.param_of, pb.param_map.data(), pb.param_map.size() * 4, hipMemcpyHostToDevice,
                                 st));
     CallResult res;

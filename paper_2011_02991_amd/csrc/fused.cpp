@@ -74,6 +74,39 @@ bool use_chain(int n, size_t amp_bytes) { return n <= chain_qubits(amp_bytes); }
 
 }  // namespace
 
+Staging::~Staging() {
+    for (Buffer &b : buffers_) {
+        (void)hipEventSynchronize(b.done);
+        (void)hipEventDestroy(b.done);
+        if (b.p) (void)hipHostFree(b.p);
+    }
+}
+
+void Staging::upload(void *dst, const std::vector<char> &image, hipStream_t st) {
+    if (image.empty()) return;
+    // the buffer used the longest ago, or a new one while that one's copy has not run
+    if (buffers_.empty() || (buffers_.size() < kMost && hipEventQuery(buffers_.front().done) != hipSuccess)) {
+        (void)hipGetLastError();   // (not ready)
+        Buffer b;
+        FCHECK(hipEventCreateWithFlags(&b.done, hipEventDisableTiming));
+        buffers_.insert(buffers_.begin(), b);
+    }
+    std::rotate(buffers_.begin(), buffers_.begin() + 1, buffers_.end());
+    Buffer &b = buffers_.back();
+    FCHECK(hipEventSynchronize(b.done));
+    if (b.bytes < image.size()) {
+        if (b.p) FCHECK(hipHostFree(b.p));
+        b.p = nullptr;
+        b.bytes = 0;
+        const size_t bytes = std::max<size_t>(image.size() * 3 / 2, 65536);
+        FCHECK(hipHostMalloc(&b.p, bytes, hipHostMallocDefault));
+        b.bytes = bytes;
+    }
+    std::memcpy(b.p, image.data(), image.size());
+    FCHECK(hipMemcpyAsync(dst, b.p, image.size(), hipMemcpyHostToDevice, st));
+    FCHECK(hipEventRecord(b.done, st));
+}
+
 size_t fused_scratch_bytes(const SweepPlan &plan, const FusedRun &fr, int M) {
     size_t b = 0;
     // the chain's images, in place of the negated matrices and the forward plan's
@@ -758,7 +791,7 @@ size_t fused_apply_scratch_bytes(const SweepPlan &a, int M) {
 
 template <typename R>
 bool run_fused_apply(const SweepPlan &a, const Circuit &c, const std::vector<Mat2> &fwd, int from, void *psi,
-                     char *scratch, size_t scratch_bytes, hipStream_t st, qng_stats *stats) {
+                     char *scratch, size_t scratch_bytes, Staging *staging, hipStream_t st, qng_stats *stats) {
     if (a.cols.empty()) return false;
     if (fused_apply_scratch_bytes(a, c.M) > scratch_bytes)
         fail(QNG_E_DEVICE, "fused apply: scratch too small (internal)");
@@ -798,8 +831,12 @@ bool run_fused_apply(const SweepPlan &a, const Circuit &c, const std::vector<Mat
     DevOp *d_ops = (DevOp *)put(a.dev_ops.data(), a.dev_ops.size() * sizeof(DevOp));
     DevMap *d_maps = (DevMap *)put(a.dev_maps.data(), a.dev_maps.size() * sizeof(DevMap));
     LaunchItem *d_items = (LaunchItem *)put(items.data(), items.size() * sizeof(LaunchItem));
-    FCHECK(hipMemcpyAsync(scratch, image.data(), image.size(), hipMemcpyHostToDevice, st));
-    FCHECK(hipStreamSynchronize(st));   // the image is released at return
+    if (staging) {
+        staging->upload(scratch, image, st);
+    } else {
+        FCHECK(hipMemcpyAsync(scratch, image.data(), image.size(), hipMemcpyHostToDevice, st));
+        FCHECK(hipStreamSynchronize(st));   // the image is released at return
+    }
     for (size_t t = 0; t < items.size(); ++t) {
         launch_sweep_pass_states<R>(d_items + t, 1, tiles, d_passes, d_ops, d_maps, (const double *)d_mats,
                                     (const float *)d_mats, a.m, a.rb, 0, st, a.ctrl);
@@ -809,9 +846,9 @@ bool run_fused_apply(const SweepPlan &a, const Circuit &c, const std::vector<Mat
 }
 
 template bool run_fused_apply<double>(const SweepPlan &, const Circuit &, const std::vector<Mat2> &, int, void *, char *,
-                                      size_t, hipStream_t, qng_stats *);
+                                      size_t, Staging *, hipStream_t, qng_stats *);
 template bool run_fused_apply<float>(const SweepPlan &, const Circuit &, const std::vector<Mat2> &, int, void *, char *,
-                                     size_t, hipStream_t, qng_stats *);
+                                     size_t, Staging *, hipStream_t, qng_stats *);
 
 size_t fused_gradient_scratch_bytes(const SweepPlan &g, int M) {
     size_t b = 0;

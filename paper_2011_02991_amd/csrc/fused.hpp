@@ -12,6 +12,27 @@
 
 namespace qng {
 
+// Copies of host images that a call does not wait for: each goes through a pinned
+// buffer of its own until the copy has run.  A context holds up to kMost buffers
+// (more calls in flight than that wait for the oldest) and frees them with itself.
+class Staging {
+  public:
+    Staging() = default;
+    Staging(const Staging &) = delete;
+    Staging &operator=(const Staging &) = delete;
+    ~Staging();
+    void upload(void *dst, const std::vector<char> &image, hipStream_t st);
+
+  private:
+    static constexpr size_t kMost = 16;
+    struct Buffer {
+        void *p = nullptr;
+        size_t bytes = 0;
+        hipEvent_t done = nullptr;   // after the buffer's last copy
+    };
+    std::vector<Buffer> buffers_;   // in the order of their last use
+};
+
 struct FusedBuffers {
     char *states = nullptr;        // state 0 = psi; column b of a group uses states 1+2b (lambda), 2+2b (phi)
     size_t state_bytes = 0;
@@ -83,10 +104,11 @@ size_t fused_apply_scratch_bytes(const SweepPlan &a, int M);
 
 // psi <- the gates of the plan a (build_apply_plan) in tile passes.  Rotations
 // with cos(theta/2) < 0 are applied negated; returns true when that leaves psi
-// negated (E and the gradient are quadratic in psi and do not see it).
+// negated (E and the gradient are quadratic in psi and do not see it).  The images
+// go up through `staging`; without one the call waits for the stream.
 template <typename R>
 bool run_fused_apply(const SweepPlan &a, const Circuit &c, const std::vector<Mat2> &fwd, int from, void *psi,
-                     char *scratch, size_t scratch_bytes, hipStream_t st, qng_stats *stats);
+                     char *scratch, size_t scratch_bytes, Staging *staging, hipStream_t st, qng_stats *stats);
 
 size_t fused_gradient_scratch_bytes(const SweepPlan &g, int M);
 

@@ -67,3 +67,70 @@ def test_tile_too_small_for_a_plan(env, tile, prec):
                 check(env, pr, prec, E, psi)
     finally:
         ctx.set_option(q.OPT_TILE_QUBITS, 0)
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+def test_returns_without_waiting(env, prec):
+    """Calls behind earlier work of their stream come back before it is done, and
+    more of them than there are staging buffers give each its own result."""
+    q, _, torch = env
+    pr = W.make_problem("layers", 13, 3, (W.RX, W.RY), "cnot_chain", 4, 9810)
+    rng = np.random.default_rng(9811)
+    thetas = [pr.theta] + [rng.uniform(0, 2 * np.pi, pr.n_params) for _ in range(23)]
+    circ = q.Circuit.from_problem(pr)
+    stream = torch.cuda.Stream()
+    ctx = q.Context(0)
+    ctx.set_stream(stream.cuda_stream)
+    outs = [outputs(torch, 13) for _ in thetas]
+    big = torch.randn(8192, 8192, device="cuda")
+    torch.cuda.synchronize()
+    ctx.energy_dev(circ, thetas[0], outs[0][0].data_ptr(), outs[0][1].data_ptr(), prec=prec)
+    with torch.cuda.stream(stream):
+        for _ in range(20):
+            busy = big @ big
+        done = torch.cuda.Event()
+        done.record(stream)
+    for k, (th, (E, psi)) in enumerate(zip(thetas, outs)):
+        ctx.energy_dev(circ, th, E.data_ptr(), psi.data_ptr(), prec=prec)
+        if k == 7:
+            waited = done.query()
+    torch.cuda.synchronize()
+    del busy
+    for th, (E, psi) in zip(thetas, outs):
+        pr.theta = th
+        check(env, pr, prec, E, psi)
+    ctx.close()
+    assert not waited
+
+
+@pytest.mark.parametrize("params", [True, False])
+def test_captured(env, params):
+    """Captured into a graph (a stream under capture cannot be waited for),
+    replayed with eager calls and synchronisations in between."""
+    q, _, torch = env
+    pr = W.make_problem("layers", 13, 2, (W.RX, W.RY), "cnot_chain", 4, 9812)
+    pr.in_state = W.random_state(13, 93)
+    if not params:
+        pr.gates, pr.theta = pr.gates[pr.gates[:, 3] < 0], np.zeros(0)
+    circ = q.Circuit.from_problem(pr)
+    ctx = q.Context(0)
+    ins = torch.tensor(pr.in_state, device="cuda")
+    E, psi = outputs(torch, 13)
+    args = (circ, pr.theta, E.data_ptr(), psi.data_ptr(), ins.data_ptr())
+    stream = torch.cuda.Stream()
+    ctx.set_stream(stream.cuda_stream)
+    ctx.energy_dev(*args)               # the workspace is there
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        ctx.energy_dev(*args)
+    for _ in range(4):
+        E.zero_()
+        psi.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        check(env, pr, "c128", E, psi)
+        ctx.energy_dev(*args)
+        ctx.synchronize()
+        check(env, pr, "c128", E, psi)
+    ctx.close()
