@@ -134,3 +134,33 @@ def test_captured(env, params):
         ctx.synchronize()
         check(env, pr, "c128", E, psi)
     ctx.close()
+
+
+def string_problem(n, strings, letters, rotations=True, seed=9820):
+    """`strings` string rotations of `letters` letters each, after an RX each."""
+    rng = np.random.default_rng(seed + n + letters)
+    rows, table = [], np.zeros((strings, n), np.uint8)
+    for k in range(strings):
+        if rotations:
+            rows.append((W.RX, int(rng.integers(0, n)), -1, len(rows)))
+        table[k, rng.choice(n, letters, replace=False)] = rng.integers(1, 4, letters)
+        rows.append((W.RPAULI, k, -1, len(rows)))
+    return W.Problem("strings%d" % letters, n, np.asarray(rows, np.int32), rng.uniform(0, 2 * np.pi, len(rows)),
+                     rng.integers(0, 4, (4, n)).astype(np.uint8), rng.standard_normal(4), strings=table)
+
+
+@pytest.mark.parametrize("n,strings,letters,rotations,passes", [
+    (10, 8, 1, True, True), (10, 8, 2, True, True), (14, 16, 1, True, True),
+    (10, 1, 2, False, False), (10, 8, 10, False, False), (14, 8, 14, False, False), (20, 8, 6, False, False)])
+def test_strings_by_the_cheaper_path(env, n, strings, letters, rotations, passes):
+    """Short strings run rewritten in tile passes, long ones as one kernel each:
+    counted by the launches (init, copy, H and its sum besides)."""
+    q, ctx, torch = env
+    pr = string_problem(n, strings, letters, rotations)
+    E, psi = outputs(torch, n)
+    ctx.energy_dev(q.Circuit.from_problem(pr), pr.theta, E.data_ptr(), psi.data_ptr())
+    torch.cuda.synchronize()
+    launches = ctx.stats()["other_launches"]
+    print(n, strings, letters, "gates", pr.n_gates, "launches", launches, flush=True)
+    check(env, pr, "c128", E, psi)
+    assert launches < pr.n_gates if passes else launches == pr.n_gates + 4
