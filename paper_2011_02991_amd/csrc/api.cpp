@@ -659,23 +659,25 @@ bool capturing(hipStream_t st) {
 }
 
 // Whether the energy of a circuit with Pauli strings runs as tile passes of the
-// circuit with its strings rewritten (`lowered`), in place of one kernel per gate: a
-// string of k letters becomes up to 4 k - 1 gates, so it pays for short ones only.
+// circuit with its strings rewritten, in place of one kernel per gate: a string of k
+// letters becomes up to 4 k - 1 gates, so it pays for short ones only.
 // Both costs in us as fitted to 1664 circuits of 4 to 22 qubits, strings of 1 to 22
-// letters: a kernel takes 3.5 to 4.5 and the register's way to memory and back, a
-// pass 12 with its share of the upload and the same way, a gate within a pass 0.5.
-// ZZ on 11 pairs of 12 qubits between RX layers: 0.17 ms by gates, 0.10 in passes;
-// 8 strings of 12 letters: 0.09 by gates, 0.23 in passes.  The 511 circuits that
-// the line takes measured 0.3 to 1.09 times the gates' time (one at 1.18, within
-// the noise of a 60 us call).
-bool lowered_pays(qng_ctx *ctx, const Circuit &plain, const Circuit &lowered, size_t amp) {
-    if (lowered.M < kMinFusedApply || !apply_plan_fits(lowered.n, ctx->opt_tile, (int)amp)) return false;
-    const double mib = (double)((size_t(1) << plain.n) * amp) / (1 << 20);
-    const double gates_us = plain.M * ((plain.n <= 12 ? 4.5 : 3.5) + 0.25 * mib);
-    const double ops_us = lowered.M * (0.5 + 0.012 * mib);
-    if (ops_us >= gates_us) return false;   // (not worth planning)
+// letters: a kernel takes 3.5 and the register's way to memory and back, a pass 12
+// with its share of the upload and the same way, a gate within a pass 0.5.  12
+// qubits, complex128: two layers of RX and ZZ on neighbours 0.17 ms by gates and 0.10
+// in passes, 8 strings of 12 letters 0.09 by gates and 0.23 in passes.  The 413
+// circuits on the passes' side measured at most 1.04 times the gates' time.
+bool lowered_pays(qng_ctx *ctx, const Circuit &c, size_t amp) {
+    if (!c.has_strings || !strings_lowerable(c) || !apply_plan_fits(c.n, ctx->opt_tile, (int)amp)) return false;
+    const int64_t gates = lowered_gates(c);
+    const double mib = (double)((size_t(1) << c.n) * amp) / (1 << 20);
+    const double gates_us = c.M * (3.5 + 0.25 * mib);
+    const double ops_us = gates * (0.5 + 0.012 * mib), pass_us = 12.0 + 0.25 * mib;
+    // (long strings are not worth rewriting to see)
+    if (gates < kMinFusedApply || ops_us + pass_us >= gates_us) return false;
+    const Circuit lowered = lower_strings(c);
     const auto plan = ctx->sweep_cache.get_apply(lowered, 0, ctx->opt_tile, (int)amp);
-    if (plan->dev_passes.size() * (12.0 + 0.25 * mib) + ops_us >= gates_us) return false;
+    if (plan->dev_passes.size() * pass_us + ops_us >= gates_us) return false;
     return !ctx->mem_limit || plan_layout(lowered.n, lowered.P, param_map_ints(lowered), amp, 2, false,
                                           fused_apply_scratch_bytes(*plan, lowered.M)).total <= ctx->mem_limit;
 }
@@ -1920,11 +1922,8 @@ qng_status qng_energy_dev(qng_ctx *ctx, const qng_circuit *circ, const void *in_
         if (!E_dev || !psi_dev) fail(QNG_E_INVALID_ARG, "output is NULL");
         reset_stats(ctx);
         Problem pb = make_problem(circ, theta, ham);
-        if (pb.circ.has_strings && ctx->opt_fusion != 0 && !capturing(ctx->stream)) {
-            Problem lowered = make_problem(circ, theta, ham, true);
-            if (!lowered.circ.has_strings && lowered_pays(ctx, pb.circ, lowered.circ, prec == QNG_C128 ? 16 : 8))
-                pb = std::move(lowered);
-        }
+        if (ctx->opt_fusion != 0 && !capturing(ctx->stream) && lowered_pays(ctx, pb.circ, prec == QNG_C128 ? 16 : 8))
+            pb = make_problem(circ, theta, ham, true);
         dispatch(prec, [&](auto tag) {
             using R = decltype(tag);
             CallSpec spec;

@@ -137,6 +137,13 @@ bool strings_lowerable(const Circuit &c) {
     return true;
 }
 
+int64_t lowered_gates(const Circuit &c) {
+    int64_t gates = c.M;
+    for (const Rot &r : c.rots)
+        if (r.string >= 0) gates += 2 * (__builtin_popcountll(r.flip) + __builtin_popcountll(r.flip | r.zy) - 1);
+    return gates;
+}
+
 Circuit lower_strings(const Circuit &c) {
     Circuit k;
     k.n = c.n;

@@ -85,6 +85,7 @@ Circuit compile_circuit(const qng_circuit *c);
 // place in the rotation order with Z_p as its generator in the rewritten frame.
 // Strings with no letter (a global phase) cannot be rewritten this way.
 bool strings_lowerable(const Circuit &c);
+int64_t lowered_gates(const Circuit &c);   // gates of lower_strings(c)
 Circuit lower_strings(const Circuit &c);
 
 // R(theta) and R(theta)^dagger for a rotation axis.
