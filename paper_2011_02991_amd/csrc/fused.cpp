@@ -66,11 +66,26 @@ struct Group {
 };
 
 // Whether the forward register's gates and the column starts run as one launch
-// per group with the state in LDS (not in the derivative-state variant): wherever
-// it fits.  Four layers of RY, RZ and a CNOT chain, metric, launches per column
-// against the chain: 2 qubits 285 -> 160 us, 10 qubits 735 -> 310 us, 13 qubits
-// 800 -> 670 us (complex128), 14 qubits 850 -> 780 us (complex64).
-bool use_chain(int n, size_t amp_bytes) { return n <= chain_qubits(amp_bytes); }
+// per group with the state in LDS (not in the derivative-state variant).  The chain
+// takes every gate through LDS on its own: 0.15 us and 8 ns per KB of state.  The
+// launches per column take about 2.5 us a column block, and the forward plan's
+// passes between them 2.5 us and 0.42 an operation, where a set of CZs is one
+// operation and a gate costs the same at any size.  So the chain loses where many
+// fixed gates lie between the rotations of a larger register.  Metric, launches
+// against the chain: 10 qubits, four layers of RY, RZ and a CNOT chain 735 and 310
+// us; 14 qubits, complex64, 24 rotations with no fixed gates between them 197 and
+// 195, with 10 CZs after each 305 and 625, with 160 CNOTs 9.8 and 12.2 ms.  Over 468
+// random circuits of 6 to 14 qubits the line costs 0.3 % against the better of the
+// two.  Circuits with controlled rotations have no forward plan: a launch per gate
+// costs more than the chain's at any size.
+bool use_chain(const SweepPlan &plan, const Circuit &c, size_t amp_bytes) {
+    if (plan.n > chain_qubits(amp_bytes)) return false;
+    if (!plan.forward) return true;
+    const double gate_us = 0.15 + 0.008 * (double)((amp_bytes << plan.n) >> 10);
+    const SweepPlan &f = *plan.forward;
+    return (c.rots[c.P - 1].pos - c.rots[0].pos) * gate_us <
+           2.5 * (double)(plan.cols.size() + f.dev_passes.size()) + 0.42 * (double)f.dev_ops.size();
+}
 
 }  // namespace
 
@@ -178,7 +193,7 @@ int run_fused_metric(const SweepPlan &plan, const FusedRun &fr, const Circuit &c
     // them up, instead of one after each seed (17 qubits, complex64, 255 columns:
     // 2960 -> 2830 us)
     const size_t nb = (size_t)reduce_blocks(n);
-    const bool chain = !states && use_chain(n, V >> n);
+    const bool chain = !states && use_chain(plan, c, V >> n);
     const bool seeds_together =
         !states && !chain && (size_t)std::min(B, std::max(1, blk_end - blk_begin)) * nb <= fr.partial_elems;
     auto controlled_start = [&](int s) { return c.rots[s].ctrl >= 0 || c.rots[s - 1].ctrl >= 0; };
