@@ -1678,22 +1678,22 @@ qng_status qng_step(qng_ctx *ctx, const qng_circuit *circ, const double *in_stat
             spec.device_solve = spec.solve_optional = solve_on_device((double)NP * NP * NP);
             hipStream_t st = ctx->stream;
             CallResult r = run<R>(ctx, pb, spec);
-            auto t0 = Clock::now();
             solved = r.solve != nullptr;
+            if (P && !solved)
+                HIPCHECK(hipMemcpyAsync(graw.data(), r.graw, (size_t)P * 16, hipMemcpyDeviceToHost, st));
+            if (NP && (G_out || !solved)) {
+                G.resize(2 * (size_t)NP * NP);
+                HIPCHECK(hipMemcpyAsync(G.data(), r.G, (size_t)NP * NP * 16, hipMemcpyDeviceToHost, st));
+            }
+            HIPCHECK(hipMemcpyAsync(e.data(), r.eraw, 16, hipMemcpyDeviceToHost, st));
+            auto t0 = Clock::now();
             if (solved) {
                 const SolveItem sv = solve_item(r, NP);
                 device_grad(r, pb, const_cast<double *>(sv.grad), st);
                 launch_shifted_solve(sv, tikhonov, dt, st);
                 // x, grad and the status word lie one after another
                 HIPCHECK(hipMemcpyAsync(xg.data(), sv.x, (size_t)NP * 16 + 4, hipMemcpyDeviceToHost, st));
-            } else if (P) {
-                HIPCHECK(hipMemcpyAsync(graw.data(), r.graw, (size_t)P * 16, hipMemcpyDeviceToHost, st));
             }
-            if (NP && (G_out || !solved)) {
-                G.resize(2 * (size_t)NP * NP);
-                HIPCHECK(hipMemcpyAsync(G.data(), r.G, (size_t)NP * NP * 16, hipMemcpyDeviceToHost, st));
-            }
-            HIPCHECK(hipMemcpyAsync(e.data(), r.eraw, 16, hipMemcpyDeviceToHost, st));
             HIPCHECK(hipStreamSynchronize(st));
             ctx->stats.solve_ms = ms_since(t0);
         });
@@ -1794,36 +1794,6 @@ qng_status qng_step_batched(qng_ctx *ctx, int32_t B, const qng_circuit *circs, c
                 e.finish_energy_grad(batch_final_pos(pb.circ), true, nullptr);
             }
             solved = L.device_solve;
-            if (solved) {
-                std::vector<SolveItem> items(B);
-                int max_np = 0;
-                for (int b = 0; b < B; ++b) {
-                    const int NP = pbs[b].circ.NP;
-                    SolveItem &it = items[b];
-                    it.G = run.G[b];
-                    it.P = NP;
-                    it.A = (double *)(base + L.solve_a[b]);
-                    it.x = (double *)(base + L.xg) + L.xg_off[b];
-                    it.grad = it.x + NP;
-                    it.status = (int32_t *)(it.x + 2 * (size_t)NP);
-                    max_np = std::max(max_np, NP);
-                    CallResult r;
-                    r.graw = (double *)(base + L.graw[b]);
-                    r.param_of = (const int *)(base + L.param_of[b]);
-                    device_grad(r, pbs[b], const_cast<double *>(it.grad), ctx->stream);
-                }
-                if (max_np) {
-                    HIPCHECK(hipMemcpyAsync(base + L.solve_items, items.data(), (size_t)B * sizeof(SolveItem),
-                                            hipMemcpyHostToDevice, ctx->stream));
-                    HIPCHECK(hipStreamSynchronize(ctx->stream));   // `items` is released at the block's end
-                    launch_shifted_solves((const SolveItem *)(base + L.solve_items), B, max_np, tikhonov, dt,
-                                          ctx->stream);
-                }
-                xg.assign(L.xg_doubles, 0.0);
-                xg_off = L.xg_off;
-                HIPCHECK(hipMemcpyAsync(xg.data(), base + L.xg, L.xg_doubles * 8, hipMemcpyDeviceToHost,
-                                        ctx->stream));
-            }
             for (int b = 0; b < B; ++b) {
                 const int P = pbs[b].circ.P, NP = pbs[b].circ.NP;
                 if (!P) continue;
@@ -1839,8 +1809,39 @@ qng_status qng_step_batched(qng_ctx *ctx, int32_t B, const qng_circuit *circs, c
                 }
             }
             HIPCHECK(hipMemcpyAsync(E.data(), base + L.eraw, (size_t)B * 16, hipMemcpyDeviceToHost, ctx->stream));
-            HIPCHECK(hipStreamSynchronize(ctx->stream));
+            std::vector<SolveItem> items(solved ? B : 0);
+            int max_np = 0;
+            if (solved) {
+                for (int b = 0; b < B; ++b) {
+                    const int NP = pbs[b].circ.NP;
+                    SolveItem &it = items[b];
+                    it.G = run.G[b];
+                    it.P = NP;
+                    it.A = (double *)(base + L.solve_a[b]);
+                    it.x = (double *)(base + L.xg) + L.xg_off[b];
+                    it.grad = it.x + NP;
+                    it.status = (int32_t *)(it.x + 2 * (size_t)NP);
+                    max_np = std::max(max_np, NP);
+                    CallResult r;
+                    r.graw = (double *)(base + L.graw[b]);
+                    r.param_of = (const int *)(base + L.param_of[b]);
+                    device_grad(r, pbs[b], const_cast<double *>(it.grad), ctx->stream);
+                }
+                HIPCHECK(hipMemcpyAsync(base + L.solve_items, items.data(), (size_t)B * sizeof(SolveItem),
+                                        hipMemcpyHostToDevice, ctx->stream));
+            }
+            HIPCHECK(hipStreamSynchronize(ctx->stream));   // the items are released at the block's end
             ctx->stats.grad_ms = ms_since(t0);
+            t0 = Clock::now();
+            if (solved) {
+                launch_shifted_solves((const SolveItem *)(base + L.solve_items), B, max_np, tikhonov, dt, ctx->stream);
+                xg.assign(L.xg_doubles, 0.0);
+                xg_off = L.xg_off;
+                HIPCHECK(hipMemcpyAsync(xg.data(), base + L.xg, L.xg_doubles * 8, hipMemcpyDeviceToHost,
+                                        ctx->stream));
+                HIPCHECK(hipStreamSynchronize(ctx->stream));
+                ctx->stats.solve_ms = ms_since(t0);
+            }
         });
         auto t0 = Clock::now();
         // every member is solved before any output is written, so a member
@@ -1881,7 +1882,7 @@ qng_status qng_step_batched(qng_ctx *ctx, int32_t B, const qng_circuit *circs, c
             }
             if (E_out) E_out[b] = E[2 * b];
         }
-        ctx->stats.solve_ms = ms_since(t0);
+        if (!solved) ctx->stats.solve_ms = ms_since(t0);
     });
 }
 
