@@ -156,7 +156,7 @@ struct Layout {
     size_t partials = 0;    // reduction scratch
     size_t lraw = 0, traw = 0, graw = 0, eraw = 0, gout = 0, tout = 0, param_of = 0;
     size_t sweep = 0, sweep_bytes = 0;  // fused-sweep descriptors and partial sums
-    size_t solve = 0;       // device solve of the step: A (NP*NP), y, x, grad (NP each), status
+    size_t solve = 0;       // device solve of the step: A ((NP + 1) * NP), x, grad (NP each), status (solve_item)
     size_t total = 0;
 };
 
@@ -933,8 +933,16 @@ void device_grad(const CallResult &r, const Problem &pb, double *grad, hipStream
 // the device's launches, so their host times add up against one chain.
 inline bool solve_on_device(double sum_np3) { return sum_np3 >= 128.0 * 128.0 * 128.0; }
 
+// Fails as the host solve does when a device solve's status words say so.
+void check_solved(const double *status_words, const std::string &of) {
+    int32_t status[2];
+    std::memcpy(status, status_words, sizeof status);
+    if (status[0] != 0)
+        fail(QNG_E_NOT_SPD, of + "Re G + eps I is not positive definite (pivot " + std::to_string(status[1]) + ")");
+}
+
 // The step's solve in its workspace: A with the right-hand side's row
-// ((NP + 1) * NP), then x and grad (NP each) and the status word.
+// ((NP + 1) * NP), then x and grad (NP each) and the status words.
 SolveItem solve_item(const double *G, char *solve, int NP) {
     SolveItem s{};
     s.G = G;
@@ -982,7 +990,7 @@ int member_tile(const Circuit &c, int opt_tile, int amp, bool f64) {
 struct BatchLayout {
     std::vector<size_t> psi, traw, graw, gout, tout, param_of, lraw_class;
     // device solves (none when they do not fit): per member A, and x, grad and
-    // the status word of all members one after another (xg_off: in doubles)
+    // the status words of all members one after another (xg_off: in doubles)
     std::vector<size_t> solve_a, xg_off;
     size_t xg = 0, xg_doubles = 0, solve_items = 0;
     bool device_solve = false;
@@ -1691,16 +1699,14 @@ qng_status qng_step(qng_ctx *ctx, const qng_circuit *circ, const double *in_stat
                 const SolveItem sv = solve_item(r, NP);
                 device_grad(r, pb, const_cast<double *>(sv.grad), st);
                 launch_shifted_solve(sv, tikhonov, dt, st);
-                // x, grad and the status word lie one after another
-                HIPCHECK(hipMemcpyAsync(xg.data(), sv.x, (size_t)NP * 16 + 4, hipMemcpyDeviceToHost, st));
+                // x, grad and the status words lie one after another
+                HIPCHECK(hipMemcpyAsync(xg.data(), sv.x, (size_t)NP * 16 + 8, hipMemcpyDeviceToHost, st));
             }
             HIPCHECK(hipStreamSynchronize(st));
             ctx->stats.solve_ms = ms_since(t0);
         });
         if (solved) {
-            int32_t status = 0;
-            std::memcpy(&status, xg.data() + 2 * (size_t)NP, 4);
-            if (status != 0) fail(QNG_E_NOT_SPD, "Re G + eps I is not positive definite (device solve)");
+            check_solved(xg.data() + 2 * (size_t)NP, "");
             std::memcpy(x.data(), xg.data(), (size_t)NP * 8);
             std::memcpy(grad.data(), xg.data() + NP, (size_t)NP * 8);
         } else {
@@ -1855,11 +1861,7 @@ qng_status qng_step_batched(qng_ctx *ctx, int32_t B, const qng_circuit *circs, c
             if (!NP) continue;
             if (solved) {
                 const double *v = xg.data() + xg_off[b];
-                int32_t status = 0;
-                std::memcpy(&status, v + 2 * (size_t)NP, 4);
-                if (status != 0)
-                    fail(QNG_E_NOT_SPD, "ansatz " + std::to_string(b) +
-                                            ": Re G + eps I is not positive definite (device solve)");
+                check_solved(v + 2 * (size_t)NP, "ansatz " + std::to_string(b) + ": ");
                 std::memcpy(xs[b].data(), v, (size_t)NP * 8);
                 std::memcpy(grads[b].data(), v + NP, (size_t)NP * 8);
                 continue;

@@ -22,8 +22,8 @@
 // both latency; k_solve_back 46 us).  Systems of a batch share every launch.
 //
 // A non-positive or non-finite pivot sets the system's status word to
-// QNG_E_NOT_SPD and the later kernels leave that system alone; k_copy_if_ok
-// lets every output follow the status.
+// QNG_E_NOT_SPD and the word after it to the pivot's number, and the later kernels
+// leave that system alone; k_copy_if_ok lets every output follow the status.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kInitThreads) void k_solve_init(const SolveItem *it
         if (i == P) s.A[idx] = -dt * s.grad[j];
         else if (j <= i) s.A[idx] = s.G[2 * idx] + (i == j ? eps : 0.0);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *s.status = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) s.status[0] = s.status[1] = 0;
 }
 
 __global__ __launch_bounds__(kPanelThreads) void k_solve_panel(const SolveItem *items, SolveItem one, int k0) {
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_solve_panel(const SolveItem *
     // L, so the row solves read consecutive entries) and its reciprocal diagonal
     __shared__ __align__(16) double D[kNB][kNB + 2];
     __shared__ double inv[kNB];
-    __shared__ int bad;
+    __shared__ int bad;   // first bad pivot of the block (-1: none)
     const int tid = threadIdx.x;
     double *A = s.A;
     // rows and columns beyond nb: the identity
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_solve_panel(const SolveItem *
         const int i = t / kNB, j = t % kNB;
         D[i][j] = (i < nb && j <= i) ? A[(int64_t)(k0 + i) * P + k0 + j] : (i == j ? 1.0 : 0.0);
     }
-    if (tid == 0) bad = 0;
+    if (tid == 0) bad = -1;
     __syncthreads();
     if (tid < 64) {
         // lane i holds row i of the block; the entries of column k pass between
@@ -91,13 +91,13 @@ __global__ __launch_bounds__(kPanelThreads) void k_solve_panel(const SolveItem *
         double r[kNB];
 #pragma unroll
         for (int j = 0; j < kNB; ++j) r[j] = D[i][j];
-        int fail = 0;
+        int first = -1;
 #pragma unroll
         for (int k = 0; k < kNB; ++k) {
             const double d = from_lane(r[k], k);
-            if (!(d > 0.0) || !isfinite(d)) fail = 1;
+            if ((!(d > 0.0) || !isfinite(d)) && first < 0) first = k;
             // (lanes above the diagonal carry values nobody reads)
-            const double l = r[k] * (1.0 / (fail ? 1.0 : sqrt(d)));
+            const double l = r[k] * (1.0 / (first >= 0 ? 1.0 : sqrt(d)));
             r[k] = l;
 #pragma unroll
             for (int j = k + 1; j < kNB; ++j) r[j] -= l * from_lane(l, j);
@@ -107,11 +107,14 @@ __global__ __launch_bounds__(kPanelThreads) void k_solve_panel(const SolveItem *
 #pragma unroll
             for (int j = 0; j < kNB; ++j) D[j][i] = r[j];
         }
-        if (tid == 0) bad = fail;
+        if (tid == 0) bad = first;
     }
     __syncthreads();
-    if (bad) {
-        if (tid == 0) *s.status = -7;   // QNG_E_NOT_SPD
+    if (bad >= 0) {
+        if (tid == 0) {
+            s.status[0] = -7;   // QNG_E_NOT_SPD
+            s.status[1] = k0 + bad;
+        }
         return;
     }
     for (int t = tid; t < kNB * kNB; t += kPanelThreads) {

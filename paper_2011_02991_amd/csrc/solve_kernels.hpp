@@ -11,8 +11,9 @@ namespace qng {
 // One shifted system (Re G + eps I) x = -dt grad, all in device memory.  G:
 // P x P complex row-major (its real part is used); grad: P doubles; A: scratch
 // of (P + 1) P doubles (the lower triangle and, as row P, the right-hand side);
-// x: P doubles; status: 0, or -7 (QNG_E_NOT_SPD) when the matrix is not
-// positive definite (x is then not meaningful).
+// x: P doubles; status: two words, 0 or -7 (QNG_E_NOT_SPD) when the matrix is not
+// positive definite (x is then not meaningful), and then the number of the first
+// pivot that is not positive and finite.
 struct SolveItem {
     const double *G;
     const double *grad;

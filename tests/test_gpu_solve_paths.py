@@ -50,3 +50,31 @@ def test_batch_statistics(env):
     assert s["solve_ms"] >= 0.05
     assert s["metric_ms"] + s["grad_ms"] + s["solve_ms"] <= wall
     assert all(r["G"] is None and np.isfinite(r["dtheta"]).all() for r in res)
+
+
+@pytest.mark.parametrize("zero", [3, 31, 32, 97, 143])
+def test_bad_pivot_is_named(env, zero):
+    """A rotation controlled by a qubit left in |0>, an exactly zero row of G: the
+    device solve's error names the pivot that the host's solve of the same G does,
+    alone and in a batch."""
+    q = env
+    ctx = q.Context(0)
+    pr = W.make_problem("layers", 9, 8, (W.RX, W.RY), "cz_ring", 4, 8450)
+    gates = np.insert(pr.gates, 0, [W.CRX, 9, 0, zero], axis=0)
+    gates[1:, 3] += gates[1:, 3] >= zero
+    P = pr.n_params + 1
+    circ = q.Circuit(10, gates, P, np.pad(pr.pauli, ((0, 0), (0, 1))), pr.coeff)
+    theta = np.insert(pr.theta, zero, 0.3)
+    G, _ = ctx.metric(circ, theta)
+    with pytest.raises(q.QNGError) as host:
+        q.solve_shifted(G, 0.0, np.ones(P))
+    assert host.value.name == "QNG_E_NOT_SPD" and "pivot %d)" % zero in str(host.value)
+    with pytest.raises(q.QNGError) as e:
+        ctx.step(circ, theta, DT, 0.0)
+    print(zero, e.value, flush=True)
+    assert str(e.value) == str(host.value)
+    good = q.Circuit.from_problem(pr)
+    with pytest.raises(q.QNGError) as e:
+        ctx.step_batched([good, circ], [pr.theta, theta], DT, 0.0)
+    assert e.value.name == "QNG_E_NOT_SPD" and "ansatz 1: " in str(e.value) and "pivot %d)" % zero in str(e.value)
+    ctx.close()
