@@ -306,7 +306,9 @@ qng_status qng_energy_grad(qng_ctx *ctx, const qng_circuit *circ, const double *
  * G_out (2*P*P), grad_out (P), E_out (1) are optional (NULL = not returned).
  * The solve reads Re G only; with G_out = NULL the fused passes form only the
  * real parts of the metric's inner products (half their multiply-adds), with
- * G_out the full complex G is computed and returned. */
+ * G_out the full complex G is computed and returned.  Systems of 128 parameters
+ * and more are solved on the device where its workspace fits the context's limit,
+ * others on the host: both FP64 Cholesky, equal to rounding. */
 qng_status qng_step(qng_ctx *ctx, const qng_circuit *circ, const double *in_state,
                     const qng_pauli_sum *ham, const double *theta, double dt, double tikhonov,
                     qng_precision prec, double *dtheta_out, double *G_out, double *grad_out,
@@ -317,7 +319,11 @@ qng_status qng_step(qng_ctx *ctx, const qng_circuit *circ, const double *in_stat
  * B entries; in_states[b] may be NULL (|0...0>); G_out/grad_out/E_out may be
  * NULL as a whole.  The ansaetze are swept together: every launch carries
  * tiles of several ansaetze.  Without any G output the sweeps form only the
- * real parts of the metric's inner products, as qng_step does. */
+ * real parts of the metric's inner products, as qng_step does.  An ansatz's G,
+ * grad and E do not depend on the others of the batch; the last bits of its
+ * dtheta may, as all systems are solved on the device or all on the host, by the
+ * sum of their P^3 (from that of one of 128 parameters on the device, where the
+ * workspace fits the context's limit). */
 qng_status qng_step_batched(qng_ctx *ctx, int32_t B, const qng_circuit *circs,
                             const double *const *in_states, const qng_pauli_sum *hams,
                             const double *const *thetas, double dt, double tikhonov,

@@ -1589,7 +1589,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
 // tree over the threads.  1024 threads for many tiles; one wavefront for at most
 // 256, where ten barriers of 16 wavefronts are what a task costs (17 qubits, 64
 // tiles, complex64 metric: 2830 -> 2710 us; batch of 48 small ansaetze: 17.95 ->
-// 17.1 ms).
+// 17.1 ms).  The order of a task's sum is that of its own count, whichever tasks
+// share its launch, so a batch's member has the same bits in any company.
 constexpr uint32_t kSmallTask = 256;
 
 template <int kReduceThreads>
@@ -1599,26 +1600,28 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_tasks(const ReduceTas
     __shared__ double sr[kReduceThreads], si[kReduceThreads];
     const ReduceTask t = tasks[blockIdx.x];
     const double2 *p = partials + t.off;
-    double a0 = 0.0, b0 = 0.0, a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0, a3 = 0.0, b3 = 0.0;
-    uint32_t k = threadIdx.x;
-    for (; k + 3 * kReduceThreads < t.count; k += 4 * kReduceThreads) {
-        const double2 v0 = p[k], v1 = p[k + kReduceThreads], v2 = p[k + 2 * kReduceThreads],
-                      v3 = p[k + 3 * kReduceThreads];
-        a0 += v0.x; b0 += v0.y;
-        a1 += v1.x; b1 += v1.y;
-        a2 += v2.x; b2 += v2.y;
-        a3 += v3.x; b3 += v3.y;
+    const uint32_t nt = t.count <= kSmallTask ? 64 : kReduceThreads;   // threads that sum
+    if (threadIdx.x < nt) {
+        double a0 = 0.0, b0 = 0.0, a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0, a3 = 0.0, b3 = 0.0;
+        uint32_t k = threadIdx.x;
+        for (; k + 3 * nt < t.count; k += 4 * nt) {
+            const double2 v0 = p[k], v1 = p[k + nt], v2 = p[k + 2 * nt], v3 = p[k + 3 * nt];
+            a0 += v0.x; b0 += v0.y;
+            a1 += v1.x; b1 += v1.y;
+            a2 += v2.x; b2 += v2.y;
+            a3 += v3.x; b3 += v3.y;
+        }
+        for (; k < t.count; k += nt) {
+            const double2 v = p[k];
+            a0 += v.x;
+            b0 += v.y;
+        }
+        sr[threadIdx.x] = (a0 + a1) + (a2 + a3);
+        si[threadIdx.x] = (b0 + b1) + (b2 + b3);
     }
-    for (; k < t.count; k += kReduceThreads) {
-        const double2 v = p[k];
-        a0 += v.x;
-        b0 += v.y;
-    }
-    sr[threadIdx.x] = (a0 + a1) + (a2 + a3);
-    si[threadIdx.x] = (b0 + b1) + (b2 + b3);
     __syncthreads();
-    for (int w = kReduceThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
+    for (uint32_t w = nt / 2; w > 0; w >>= 1) {
+        if (threadIdx.x < w) {
             sr[threadIdx.x] += sr[threadIdx.x + w];
             si[threadIdx.x] += si[threadIdx.x + w];
         }
