@@ -668,7 +668,7 @@ bool capturing(hipStream_t st) {
 // in passes, 8 strings of 12 letters 0.09 by gates and 0.23 in passes.  The 413
 // circuits on the passes' side measured at most 1.04 times the gates' time.
 bool lowered_pays(qng_ctx *ctx, const Circuit &c, size_t amp) {
-    if (!c.has_strings || !strings_lowerable(c) || !apply_plan_fits(c.n, ctx->opt_tile, (int)amp)) return false;
+    if (!c.has_strings || !strings_lowerable(c)) return false;
     const int64_t gates = lowered_gates(c);
     const double mib = (double)((size_t(1) << c.n) * amp) / (1 << 20);
     const double gates_us = c.M * (3.5 + 0.25 * mib);
@@ -676,7 +676,7 @@ bool lowered_pays(qng_ctx *ctx, const Circuit &c, size_t amp) {
     // (long strings are not worth rewriting to see)
     if (gates < kMinFusedApply || ops_us + pass_us >= gates_us) return false;
     const Circuit lowered = lower_strings(c);
-    const auto plan = ctx->sweep_cache.get_apply(lowered, 0, ctx->opt_tile, (int)amp);
+    const auto plan = ctx->sweep_cache.get_apply(lowered, 0, (int)amp);
     if (plan->dev_passes.size() * pass_us + ops_us >= gates_us) return false;
     return !ctx->mem_limit || plan_layout(lowered.n, lowered.P, param_map_ints(lowered), amp, 2, false,
                                           fused_apply_scratch_bytes(*plan, lowered.M)).total <= ctx->mem_limit;
@@ -759,7 +759,7 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
     }
     // the forward pass to psi (after a metric: the gates behind its last
     // rotation) in tile passes where that saves launches, i.e. passes over the
-    // register, and the tile width asked for can hold them
+    // register
     std::shared_ptr<const SweepPlan> aplan;
     const int aplan_from = spec.metric && c.P ? c.rots[c.P - 1].pos : 0;
     const size_t scratch_without_apply = scratch;
@@ -767,8 +767,8 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
     // kernels carry their matrices as arguments, which a replay finds unchanged
     const bool energy_only = spec.psi_out_dev && !spec.grad && !spec.metric;
     if (ctx->opt_fusion != 0 && !(energy_only && capturing(ctx->stream)) && !c.has_strings && !spec.psi_final_dev && (spec.grad || spec.psi_out_dev) &&
-        c.M - aplan_from >= kMinFusedApply && apply_plan_fits(n, ctx->opt_tile, (int)amp)) {
-        aplan = ctx->sweep_cache.get_apply(c, aplan_from, ctx->opt_tile, (int)amp);
+        c.M - aplan_from >= kMinFusedApply) {
+        aplan = ctx->sweep_cache.get_apply(c, aplan_from, (int)amp);
         scratch = std::max(scratch, fused_apply_scratch_bytes(*aplan, c.M));
     }
     // circuits the fused passes do not take: one kernel per sweep step, with up

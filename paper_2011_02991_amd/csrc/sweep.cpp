@@ -615,32 +615,19 @@ int register_bits(int m, int /*amp_bytes*/) {
 
 namespace {
 
-// Qubits per tile: the option's (0: the default `def`), at most max_m (the widest
-// tile the plan's kernels take) and the register.
-int tile_width(int n, int tile_qubits, int def, int max_m) {
-    return std::min({tile_qubits > 0 ? tile_qubits : def, max_m, n});
-}
-
-// Lowest qubits kept in every tile, so that its loads and stores are runs of
-// consecutive amplitudes.
-int carrier_qubits(int n, int m, int amp_bytes) { return n > m ? std::min(amp_bytes >= 16 ? 3 : 4, m - 1) : 0; }
-
-// Why tiles of m qubits cannot hold a plan (nullptr: they can).
-const char *tile_error(int n, int m, int amp_bytes) {
-    if (n - m > kMaxRest) return "tile too small for this register (at most 24 qubits outside a tile)";
-    if (n > m && m - carrier_qubits(n, m, amp_bytes) < 2) return "tile too small for the carrier qubits";
-    return nullptr;
-}
-
 // Tile width, register bits and carriers of a plan for a register of c.n qubits.
+// max_m: widest tile the kernels of this plan take.
 void plan_shape(SweepPlan &plan, const Circuit &c, int tile_qubits, int amp_bytes, bool reg_f64, int max_m) {
     plan.n = c.n;
     plan.P = c.P;
-    const int m = tile_width(c.n, tile_qubits, default_tile_qubits(c.n, amp_bytes, reg_f64), max_m);
-    if (const char *why = tile_error(c.n, m, amp_bytes)) fail(QNG_E_INVALID_ARG, why);
+    int m = tile_qubits > 0 ? tile_qubits : default_tile_qubits(c.n, amp_bytes, reg_f64);
+    if (m > max_m) m = max_m;
+    if (m > c.n) m = c.n;
+    if (c.n - m > kMaxRest) fail(QNG_E_INVALID_ARG, "tile too small for this register (at most 24 qubits outside a tile)");
     plan.m = m;
     plan.rb = register_bits(m, amp_bytes);
-    plan.carriers = carrier_qubits(c.n, m, amp_bytes);
+    plan.carriers = c.n > m ? std::min(amp_bytes >= 16 ? 3 : 4, m - 1) : 0;
+    if (c.n > m && m - plan.carriers < 2) fail(QNG_E_INVALID_ARG, "tile too small for the carrier qubits");
 }
 
 ColumnPlan plan_column(const Circuit &c, const SweepPlan &plan, int s, const std::vector<Event> &ev,
@@ -773,16 +760,13 @@ SweepPlan build_forward_plan(const Circuit &c, const std::vector<int> &tops, int
 // so once per 35-130 gates (25 qubits, 592 gates: 8 passes).  Measured, energy
 // and gradient: 25 qubits complex64 55.5 -> 15.8 ms, 20 qubits complex128 (600
 // gates) 4.00 -> 1.53 ms, 12 qubits (216 gates, launch-bound) 0.96 -> 0.42 ms.
-constexpr int kApplyTile = 12;
-
-bool apply_plan_fits(int n, int tile_qubits, int amp_bytes) {
-    return !tile_error(n, tile_width(n, tile_qubits, kApplyTile, kApplyTile), amp_bytes);
-}
-
-SweepPlan build_apply_plan(const Circuit &c, int from, int tile_qubits, int amp_bytes) {
+// The tile option is not the forward pass's: every register has a plan (33 qubits
+// are 21 outside a tile), and in tiles of 6 qubits the passes of a circuit of 18 cost
+// more than its gates (two layers of RX and ZZ: 0.33 ms by gates, 0.51 in passes).
+SweepPlan build_apply_plan(const Circuit &c, int from, int amp_bytes) {
     SweepPlan plan;
     plan.width = 0;
-    plan_shape(plan, c, tile_qubits > 0 ? tile_qubits : kApplyTile, amp_bytes, amp_bytes == 16, kApplyTile);
+    plan_shape(plan, c, 12, amp_bytes, amp_bytes == 16, 12);
     std::vector<Event> ev;
     for (int k = from; k < c.M; ++k) ev.push_back(unapply_event(c, k));
     if (!ev.empty()) plan.cols.push_back(plan_column(c, plan, c.P, ev, SlotDest{1, 0, 0}));
@@ -960,10 +944,10 @@ std::shared_ptr<const SweepPlan> SweepCache::get_gradient(const Circuit &c, int 
     return look_up(key, [&] { return build_gradient_plan(c, tile_qubits, amp_bytes, reg_f64); });
 }
 
-std::shared_ptr<const SweepPlan> SweepCache::get_apply(const Circuit &c, int from, int tile_qubits, int amp_bytes) {
-    std::vector<int32_t> key = {-3, from, tile_qubits, amp_bytes};
+std::shared_ptr<const SweepPlan> SweepCache::get_apply(const Circuit &c, int from, int amp_bytes) {
+    std::vector<int32_t> key = {-3, from, amp_bytes};
     append_structure_key(c, key);
-    return look_up(key, [&] { return build_apply_plan(c, from, tile_qubits, amp_bytes); });
+    return look_up(key, [&] { return build_apply_plan(c, from, amp_bytes); });
 }
 
 FusedRun fused_config(const SweepPlan &plan, int requested_streams, size_t state_bytes, size_t free_bytes) {

@@ -275,10 +275,7 @@ SweepPlan build_gradient_plan(const Circuit &c, int tile_qubits, int amp_bytes, 
 
 // Plan of the gates at positions [from, M) applied in order to one register (a
 // plan of width 0 with one column; its gate table holds the gates themselves).
-SweepPlan build_apply_plan(const Circuit &c, int from, int tile_qubits, int amp_bytes);
-
-// Whether tiles of the given width (0: the default) can hold such a plan.
-bool apply_plan_fits(int n, int tile_qubits, int amp_bytes);
+SweepPlan build_apply_plan(const Circuit &c, int from, int amp_bytes);
 
 // Plans by circuit structure.  Every look-up hands out an owning pointer and may
 // evict any other plan: a caller holds what it looked up for as long as it uses it.
@@ -297,7 +294,7 @@ struct SweepCache {
                                                 bool reg_f64, int width = 1,
                                                 const std::vector<int> *rot_block = nullptr);
     std::shared_ptr<const SweepPlan> get_gradient(const Circuit &c, int tile_qubits, int amp_bytes, bool reg_f64);
-    std::shared_ptr<const SweepPlan> get_apply(const Circuit &c, int from, int tile_qubits, int amp_bytes);
+    std::shared_ptr<const SweepPlan> get_apply(const Circuit &c, int from, int amp_bytes);
 
   private:
     template <typename F> std::shared_ptr<const SweepPlan> look_up(const std::vector<int32_t> &key, F build);

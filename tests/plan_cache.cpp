@@ -3,8 +3,7 @@
 //   use    the plans of 400 distinct circuits, each read after its last look-up
 //   round  128 circuits over and over: no plan is built twice
 //   oldest one circuit more evicts the plans not looked up for the longest time
-//   tiles  apply_plan_fits says for every register and tile width whether a plan
-//          of the forward pass can be built
+//   registers  the forward pass of every register has a plan
 // Prints "ok".
 #include <cstdio>
 #include <cstring>
@@ -51,7 +50,7 @@ Plans look_up(SweepCache &cache, int k) {
     Plans p;
     p.metric = cache.get_shared(c, 0, 16, 1, true, 2);
     p.gradient = cache.get_gradient(c, 0, 16, true);
-    p.apply = cache.get_apply(c, c.rots[c.P - 1].pos, 0, 16);
+    p.apply = cache.get_apply(c, c.rots[c.P - 1].pos, 16);
     return p;
 }
 
@@ -92,7 +91,7 @@ bool oldest() {
     return look_up(cache, 1).metric != first[1].metric;
 }
 
-bool tiles() {
+bool registers() {
     for (int n = 2; n <= 33; ++n) {
         std::vector<qng_gate> g;
         for (int q = 0; q < 8; ++q) g.push_back({QNG_CNOT, q % n, (q + 1) % n, -1});
@@ -101,19 +100,13 @@ bool tiles() {
         qc.n_gates = (int)g.size();
         qc.gates = g.data();
         const Circuit c = compile_circuit(&qc);
-        for (int tile = 0; tile <= 14; ++tile)
-            for (int amp : {8, 16}) {
-                bool built = true;
-                try {
-                    build_apply_plan(c, 0, tile, amp);
-                } catch (const Error &) {
-                    built = false;
-                }
-                if (built != apply_plan_fits(n, tile, amp)) {
-                    std::printf("n %d tile %d amp %d\n", n, tile, amp);
-                    return false;
-                }
-            }
+        for (int amp : {8, 16}) {
+            size_t gates = 0;
+            const SweepPlan plan = build_apply_plan(c, 0, amp);
+            for (const HostPass &hp : plan.cols.at(0).passes)
+                for (const DevOp &op : hp.ops) gates += op.type == OP_CNOT;
+            if (gates != g.size()) return false;
+        }
     }
     return true;
 }
@@ -125,7 +118,7 @@ int main(int argc, char **argv) {
     const bool ok = !std::strcmp(check, "use")      ? use()
                     : !std::strcmp(check, "round")  ? round()
                     : !std::strcmp(check, "oldest") ? oldest()
-                    : !std::strcmp(check, "tiles")  ? tiles()
+                    : !std::strcmp(check, "registers") ? registers()
                                                     : false;
     std::puts(ok ? "ok" : "failed");
     return ok ? 0 : 1;

@@ -1,4 +1,5 @@
-"""qng_energy_dev in the situations in which it cannot run as tile passes."""
+"""qng_energy_dev under the options, streams, limits and circuits that its tile passes have to
+leave as they were: small tiles, busy and captured streams, long strings."""
 import numpy as np
 import pytest
 
@@ -41,8 +42,8 @@ def outputs(torch, n):
 @pytest.mark.parametrize("prec", ["c128", "c64"])
 @pytest.mark.parametrize("tile", [1, 2, 3, 4, 5, 6])
 def test_tile_too_small_for_a_plan(env, tile, prec):
-    """Tiles that leave fewer than two qubits beside the carriers hold no plan;
-    the energy needs none (with and without rotations)."""
+    """Sweeps in tiles that leave fewer than two qubits beside the carriers have no
+    plan; the energy does not depend on their width (with and without rotations)."""
     q, ctx, torch = env
     fixed = W.random_circuit(9, 30, 9801, n_terms=4)
     gates = [g for g in fixed.gates if g[3] < 0] * 4
@@ -58,6 +59,7 @@ def test_tile_too_small_for_a_plan(env, tile, prec):
             ctx.energy_dev(circ, pr.theta, E.data_ptr(), psi.data_ptr(), in_state_dev_ptr=ins.data_ptr(), prec=prec)
             torch.cuda.synchronize()
             check(env, pr, prec, E, psi)
+            assert ctx.stats()["other_launches"] == 5      # one pass
             if not len(pr.theta):
                 E.zero_()
                 grad = torch.zeros(1, dtype=torch.float64, device="cuda")

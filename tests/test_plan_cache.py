@@ -1,7 +1,7 @@
 """The cache of sweep plans on the host (AddressSanitizer build of the planner,
 look-ups in the order of a step): a plan in use outlives its eviction, 128
-circuits keep their plans, and one more evicts those not used for the longest time; and which tile widths
-hold a plan of the forward pass."""
+circuits keep their plans, and one more evicts those not used for the longest time; and the forward
+pass of every register has a plan."""
 import os
 import subprocess
 
@@ -20,7 +20,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["use", "round", "oldest", "tiles"])
+@pytest.mark.parametrize("check", ["use", "round", "oldest", "registers"])
 def test_plan_cache(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.split()[-1] == "ok", r.stdout + r.stderr
