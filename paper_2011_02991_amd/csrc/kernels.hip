@@ -1288,8 +1288,11 @@ template <typename R> void launch_chain(const ChainItem *items, int n_items, int
     if (max_n < 1 || max_n > chain_qubits(sizeof(typename Cplx<R>::T))) throw hipErrorInvalidValue;
     const size_t lds = sizeof(typename Cplx<R>::T) << max_n;
     if (lds > 32768) {
+        // the kernel's bound is the process's: always that of the largest
+        // register, so that a call of another thread never lowers it
+        const size_t most = sizeof(typename Cplx<R>::T) << chain_qubits(sizeof(typename Cplx<R>::T));
         const hipError_t e = hipFuncSetAttribute((const void *)k_chain<R>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)lds);
+                                                 (int)most);
         if (e != hipSuccess) throw e;
     }
     const int threads = std::min(kChainThreads, std::max(64, 1 << (max_n - 1)));

@@ -45,3 +45,29 @@ def test_route(n, prec, fixed, controlled, chain):
     assert err <= tol
     # a chain is two launches a group of columns; else one or more a column block
     assert extra < 10 if chain else extra >= P // 4
+
+
+def test_two_threads_of_different_registers():
+    """Chains of 13 and 12 qubits (128 and 64 KB of LDS) started by two threads at
+    once, each on its own context: bitwise what each gives alone."""
+    import threading
+    import torch  # noqa: F401
+    import paper_2011_02991_amd as q
+    prs = [W.make_problem("layers", n, 2, (W.RY, W.RZ), "cnot_chain", 2, 9990 + n) for n in (13, 12)]
+    ctxs = [q.Context(0) for _ in prs]
+    circs = [q.Circuit.from_problem(p) for p in prs]
+    want = [c.metric(k, p.theta)[0] for c, k, p in zip(ctxs, circs, prs)]
+    same = [[], []]
+
+    def work(i):
+        for _ in range(40):
+            same[i].append(np.array_equal(ctxs[i].metric(circs[i], prs[i].theta)[0], want[i]))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for c in ctxs:
+        c.close()
+    assert [len(s) for s in same] == [40, 40] and all(same[0]) and all(same[1])
