@@ -1379,14 +1379,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
     // one (unused by ops without a gate) are fetched while the current one runs,
     // so that no handler waits for scalar loads at its start (a rotation on its
     // own is 120 instructions: a wait for its two parameters was a third of it).
-    // The kernels with controlled handlers load the current op's in place: with
-    // the next descriptor a step ahead a step of 20 qubits (complex128) takes
-    // 13.27 ms instead of 12.98 and a gradient of 24 (complex64) 4.20 instead of
-    // 4.15, a step of 21 (complex64) 18.40 instead of 18.50.
+    // The kernels with controlled handlers load the current op's in place where
+    // they form real products or none: with the next descriptor a step ahead a
+    // step of 20 qubits (complex128) takes 13.27 ms instead of 12.98 and a gradient
+    // of 24 (complex64) 4.20 instead of 4.15, with two ahead a step of 21
+    // (complex64) 19.2 instead of 18.5.  With complex products fetching ahead is
+    // the faster one: metric of 21 qubits 9.34 ms instead of 9.56 (complex128),
+    // 20.3 instead of 20.5 (complex64).
+    constexpr bool kInPlace = CTRL && (kRealProducts || kNoProducts);
     OpD nxt{}, aft{};
     const CT *nrow = mt;
     CT nu = 0, nw = 0;
-    if constexpr (!CTRL) {
+    if constexpr (!kInPlace) {
         nxt = load_op(op_ptr);
         aft = load_op(op_ptr + (n_ops > 1 ? 1 : 0));
         nrow = mt + (size_t)(nxt.gate > 0 ? nxt.gate : 0) * 8;
@@ -1394,10 +1398,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kNoPro
         nw = nrow[1];
     }
     for (int oi = 0; oi < n_ops; ++oi) {
-        const OpD op = CTRL ? load_op(op_ptr + oi) : nxt;
-        const CT *mrow = CTRL ? mt + (size_t)(op.gate > 0 ? op.gate : 0) * 8 : nrow;
-        const CT u = CTRL ? mrow[0] : nu, w = CTRL ? mrow[1] : nw;
-        if constexpr (!CTRL) {
+        const OpD op = kInPlace ? load_op(op_ptr + oi) : nxt;
+        const CT *mrow = kInPlace ? mt + (size_t)(op.gate > 0 ? op.gate : 0) * 8 : nrow;
+        const CT u = kInPlace ? mrow[0] : nu, w = kInPlace ? mrow[1] : nw;
+        if constexpr (!kInPlace) {
             nxt = aft;
             aft = load_op(op_ptr + (oi + 2 < n_ops ? oi + 2 : n_ops - 1));
             nrow = mt + (size_t)(nxt.gate > 0 ? nxt.gate : 0) * 8;
