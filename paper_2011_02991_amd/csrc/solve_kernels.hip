@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_solve_panel(const SolveItem *
     // L, so the row solves read consecutive entries) and its reciprocal diagonal
     __shared__ __align__(16) double D[kNB][kNB + 2];
     __shared__ double inv[kNB];
-    __shared__ int bad;   // first bad pivot of the block (-1: none)
+    __shared__ int bad;
     const int tid = threadIdx.x;
     double *A = s.A;
     // rows and columns beyond nb: the identity
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kPanelThreads) void k_solve_panel(const SolveItem *
         const int i = t / kNB, j = t % kNB;
         D[i][j] = (i < nb && j <= i) ? A[(int64_t)(k0 + i) * P + k0 + j] : (i == j ? 1.0 : 0.0);
     }
-    if (tid == 0) bad = -1;
+    if (tid == 0) bad = 0;
     __syncthreads();
     if (tid < 64) {
         // lane i holds row i of the block; the entries of column k pass between
@@ -91,13 +91,13 @@ __global__ __launch_bounds__(kPanelThreads) void k_solve_panel(const SolveItem *
         double r[kNB];
 #pragma unroll
         for (int j = 0; j < kNB; ++j) r[j] = D[i][j];
-        int first = -1;
+        int fail = 0;
 #pragma unroll
         for (int k = 0; k < kNB; ++k) {
             const double d = from_lane(r[k], k);
-            if ((!(d > 0.0) || !isfinite(d)) && first < 0) first = k;
+            if (!(d > 0.0) || !isfinite(d)) fail = 1;
             // (lanes above the diagonal carry values nobody reads)
-            const double l = r[k] * (1.0 / (first >= 0 ? 1.0 : sqrt(d)));
+            const double l = r[k] * (1.0 / (fail ? 1.0 : sqrt(d)));
             r[k] = l;
 #pragma unroll
             for (int j = k + 1; j < kNB; ++j) r[j] -= l * from_lane(l, j);
@@ -107,13 +107,17 @@ __global__ __launch_bounds__(kPanelThreads) void k_solve_panel(const SolveItem *
 #pragma unroll
             for (int j = 0; j < kNB; ++j) D[j][i] = r[j];
         }
-        if (tid == 0) bad = first;
+        if (tid == 0) bad = fail;
     }
     __syncthreads();
-    if (bad >= 0) {
+    if (bad) {
         if (tid == 0) {
+            // the first bad pivot is on the diagonal as it was (kept in the loop, its
+            // number would cost the chain 491 spilled scalars)
+            int k = 0;
+            while (k < nb - 1 && D[k][k] > 0.0 && isfinite(D[k][k])) ++k;
             s.status[0] = -7;   // QNG_E_NOT_SPD
-            s.status[1] = k0 + bad;
+            s.status[1] = k0 + k;
         }
         return;
     }
