@@ -217,6 +217,16 @@ char *ensure_workspace(qng_ctx *ctx, size_t bytes) {
     return (char *)p;
 }
 
+// Whether ensure_workspace would give that many bytes.
+bool workspace_fits(qng_ctx *ctx, size_t bytes) {
+    if (ctx->fixed_ws) return bytes <= ctx->fixed_ws_bytes;
+    if (ctx->mem_limit && bytes > ctx->mem_limit) return false;
+    if (bytes <= ctx->ws_bytes) return true;
+    size_t free_b = 0, total_b = 0;
+    HIPCHECK(hipMemGetInfo(&free_b, &total_b));
+    return bytes <= free_b + ctx->ws_bytes;   // (the smaller workspace is released first)
+}
+
 // -------------------------------------------------------------- the engine
 
 struct Problem {
@@ -678,8 +688,8 @@ bool lowered_pays(qng_ctx *ctx, const Circuit &c, size_t amp) {
     const Circuit lowered = lower_strings(c);
     const auto plan = ctx->sweep_cache.get_apply(lowered, 0, (int)amp);
     if (plan->dev_passes.size() * pass_us + ops_us >= gates_us) return false;
-    return !ctx->mem_limit || plan_layout(lowered.n, lowered.P, param_map_ints(lowered), amp, 2, false,
-                                          fused_apply_scratch_bytes(*plan, lowered.M)).total <= ctx->mem_limit;
+    return workspace_fits(ctx, plan_layout(lowered.n, lowered.P, param_map_ints(lowered), amp, 2, false,
+                                           fused_apply_scratch_bytes(*plan, lowered.M)).total);
 }
 
 struct CallResult {
@@ -722,7 +732,8 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
         const size_t avail = free_b + ctx->ws_bytes;
         const size_t cap = ctx->mem_limit ? std::min(avail, ctx->mem_limit) : avail;
         // the derivative-state variant: chunk_cols columns per chunk (all P - 1
-        // columns above column 0 when they fit), kept after the block registers
+        // columns above column 0 when they fit, whatever becomes of a solve that
+        // may move to the host), kept after the block registers
         auto configure = [&](int cols) {
             const size_t kept = states ? kept_states(c.P, cols) * V : 0;
             fr = fused_config(*plan, ctx->opt_streams, V, cap > kept ? cap - kept : 0);
@@ -731,7 +742,7 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
             n_block_states = std::max(4, 1 + (plan->width + 1) * fr.B);
             n_states = n_block_states + (states ? (int)kept_states(c.P, cols) : 0);
             return plan_layout(n, c.P, param_map_ints(c), amp, n_states, spec.in_host != nullptr, scratch,
-                               spec.device_solve ? c.NP : -1).total;
+                               spec.device_solve && !spec.solve_optional ? c.NP : -1).total;
         };
         if (states) {
             const int all = c.P - 1;
@@ -789,15 +800,14 @@ CallResult run(qng_ctx *ctx, const Problem &pb, CallSpec spec) {
     }
     Layout L = plan_layout(n, c.P, param_map_ints(c), amp, n_states, spec.in_host != nullptr, scratch,
                            spec.device_solve ? c.NP : -1);
-    const size_t cap_ws = ctx->fixed_ws ? ctx->fixed_ws_bytes : ctx->mem_limit;
-    if (aplan && cap_ws && L.total > cap_ws) {
+    if (aplan && !workspace_fits(ctx, L.total)) {
         // the plan's image is all that does not fit: one kernel per gate needs none
         aplan.reset();
         scratch = scratch_without_apply;
         L = plan_layout(n, c.P, param_map_ints(c), amp, n_states, spec.in_host != nullptr, scratch,
                         spec.device_solve ? c.NP : -1);
     }
-    if (spec.solve_optional && cap_ws && L.total > cap_ws) {
+    if (spec.solve_optional && !workspace_fits(ctx, L.total)) {
         spec.device_solve = false;
         L = plan_layout(n, c.P, param_map_ints(c), amp, n_states, spec.in_host != nullptr, scratch, -1);
     }
@@ -1119,7 +1129,7 @@ BatchRun batch_metric(qng_ctx *ctx, const std::vector<Problem> &pbs, const doubl
     }
     L.xg = take(L.xg_doubles * 8);
     L.solve_items = take((size_t)B * sizeof(SolveItem));
-    L.device_solve = solve_on_device(np3) && (!ctx->mem_limit || off <= ctx->mem_limit);
+    L.device_solve = solve_on_device(np3) && workspace_fits(ctx, off);
     if (L.device_solve) L.total = off;
     char *base = ensure_workspace(ctx, L.total);
     run.base = base;

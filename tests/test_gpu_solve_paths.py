@@ -157,3 +157,25 @@ def test_energy_without_room_for_the_plan(env, strings):
         assert abs(float(E) - oracle.energy(pr)) <= tol * np.abs(pr.coeff).sum()
         assert launches == pr.n_gates + 4 if limited else launches < pr.n_gates
     ctx.close()
+
+
+def test_optional_solve_takes_no_kept_state(env):
+    """The derivative-state variant at a limit with room for all its states but not
+    for the solve's matrix as well: all are kept, and the host solves."""
+    q = env
+    ctx = q.Context(0)
+    ctx.set_option(q.OPT_METHOD, 1)
+    pr = W.make_problem("layers", 9, 8, (W.RX, W.RY), "cz_ring", 4, 8490)
+    P = pr.n_params
+    circ = q.Circuit.from_problem(pr)
+    call = lambda: ctx.step(circ, pr.theta, DT, EPS)
+    ctx.set_option(q.OPT_STATE_CHUNK, P)
+    limit = least_workspace(q, ctx, call)
+    ctx.set_option(q.OPT_STATE_CHUNK, 0)
+    ctx.set_mem_limit(limit)
+    got = call()
+    chunks = ctx.stats()["state_chunks"]
+    ctx.close()
+    print(limit, chunks, flush=True)
+    assert chunks == 1
+    check(got, P)
