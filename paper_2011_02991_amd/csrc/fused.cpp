@@ -67,7 +67,7 @@ struct Group {
 
 // Whether the forward register's gates and the column starts run as one launch
 // per group with the state in LDS (not in the derivative-state variant).  The chain
-// takes every gate through LDS on its own: 0.15 us and 8 ns per KB of state.  The
+// takes every fixed gate through LDS on its own: 0.15 us and 8 ns per KB of state.  The
 // launches per column take about 2.5 us a column block, and the forward plan's
 // passes between them 2.5 us and 0.42 an operation, where a set of CZs is one
 // operation and a gate costs the same at any size.  So the chain loses where many

@@ -757,7 +757,7 @@ SweepPlan build_forward_plan(const Circuit &c, const std::vector<int> &tops, int
 // qubits in either precision: with lambda alone a thread holds 16 amplitudes of
 // FP64 without spilling, and a wider tile means fewer passes over the register.
 // One kernel per gate reads and writes the register once a gate; the passes do
-// so once per 35-130 gates (25 qubits, 592 gates: 8 passes).  Measured, energy
+// so once per 60 to 200 gates (25 qubits, 592 gates: 10 passes).  Measured, energy
 // and gradient: 25 qubits complex64 55.5 -> 15.8 ms, 20 qubits complex128 (600
 // gates) 4.00 -> 1.53 ms, 12 qubits (216 gates, launch-bound) 0.96 -> 0.42 ms.
 // The tile option is not the forward pass's: every register has a plan (33 qubits

@@ -4,7 +4,7 @@ Two modes:
 
   python profile_sweep.py run [--config 3] [--prec c64]
       One natural-gradient step of a workload without the G output (the passes
-      bench.py times), preceded by one clone of a 512 MiB state with the
+      bench.py times) or, with --want-g 1, with it, preceded by one clone of a 512 MiB state with the
       library's own copy kernel (the calibration kernel for FETCH_SIZE /
       WRITE_SIZE).  Meant to run under rocprofv3 --pmc, one counter group per
       run.
@@ -51,7 +51,7 @@ def run(args):
     ctx.set_option(qng.OPT_TILE_QUBITS, args.tile)
     ctx.set_option(qng.OPT_F64_REGISTERS, args.f64_regs)
     ctx.set_option(qng.OPT_EXACT_PRODUCTS, args.exact_products)
-    ctx.step(qng.Circuit.from_problem(pr), pr.theta, pr.dt, pr.tikhonov, prec=args.prec, want_G=False)
+    ctx.step(qng.Circuit.from_problem(pr), pr.theta, pr.dt, pr.tikhonov, prec=args.prec, want_G=bool(args.want_g))
     torch.cuda.synchronize()
     print(json.dumps({"workload": pr.name, "prec": args.prec, **ctx.stats()}), flush=True)
     ctx.close()
@@ -153,6 +153,7 @@ def main():
     r.add_argument("--tile", type=int, default=0)
     r.add_argument("--f64-regs", type=int, default=0)
     r.add_argument("--exact-products", type=int, default=1)
+    r.add_argument("--want-g", type=int, default=0, help="1: the step returns G (complex products)")
     r.add_argument("--layers", type=int, default=0, help="layers of a 26-qubit instance (0 = the full workload)")
     s = sub.add_parser("summarize")
     s.add_argument("--kind", choices=["stats", "traffic", "counters"], required=True)
