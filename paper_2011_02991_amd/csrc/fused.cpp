@@ -118,7 +118,7 @@ void Staging::upload(void *dst, const std::vector<char> &image, hipStream_t st) 
         b.bytes = bytes;
     }
     std::memcpy(b.p, image.data(), image.size());
-    FCHECK(hipMemcpyAsync(dst, b.p, image.size(), hipMemcpyHostToDevice, st));
+    launch_upload(b.p, dst, image.size(), st);
     FCHECK(hipEventRecord(b.done, st));
 }
 
@@ -848,6 +848,7 @@ bool run_fused_apply(const SweepPlan &a, const Circuit &c, const std::vector<Mat
     LaunchItem *d_items = (LaunchItem *)put(items.data(), items.size() * sizeof(LaunchItem));
     if (staging) {
         staging->upload(scratch, image, st);
+        ++stats->other_launches;
     } else {
         FCHECK(hipMemcpyAsync(scratch, image.data(), image.size(), hipMemcpyHostToDevice, st));
         FCHECK(hipStreamSynchronize(st));   // the image is released at return

@@ -56,6 +56,8 @@ template <typename R> void launch_fixed_multi(const StepRegs &regs, int n, bool 
 template <typename R> void launch_init_state(void *dst, int n, const void *src_c128, hipStream_t st);
 template <typename R> void launch_to_c128(const void *src, void *dst, int n, bool negate, hipStream_t st);
 template <typename R> void launch_copy(const void *src, void *dst, int n, hipStream_t st);
+// dst <- pinned host memory, by a kernel; both 16-byte aligned, bytes a multiple of 16.
+void launch_upload(const void *pinned, void *dst, size_t bytes, hipStream_t st);
 
 // Apply a 2x2 matrix on qubit q to one register (s1 == nullptr) or to two.
 template <typename R> void launch_apply_1q(void *s0, void *s1, int n, int q, const DevMat2 &m, hipStream_t st);
