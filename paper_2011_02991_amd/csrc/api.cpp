@@ -657,7 +657,8 @@ void unpack_to_params(const Problem &pb, const double *lraw, const double *traw,
 // Fewest gates the forward pass runs as tile passes: a gate's own launch is
 // about 3 us on a small register, a plan's one upload with its wait and a pass
 // about 25 us (the 9 gates behind the metric of the 10-qubit step: 955 us a
-// step gate by gate, 931 us in one pass; below 8 the launches win).
+// step gate by gate, 931 us in one pass; below 8 the launches win).  On registers
+// whose gates are bound by memory fewer would pay; the line is not drawn by size.
 constexpr int kMinFusedApply = 8;
 
 // Whether the stream is being captured (or cannot be asked because another is).
