@@ -34,8 +34,10 @@
  *   - Host outputs are caller-allocated; on error they are not written.
  *   - Host-pointer entry points are synchronous.  "_dev" entry points take
  *     device pointers, enqueue their work on the context's stream and return
- *     without waiting; their device outputs are valid once that stream has
- *     reached the end of the call.
+ *     without waiting for it; their device outputs are valid once that stream has
+ *     reached the end of the call.  (On the fused passes, those that form a metric
+ *     or a gradient wait within the call for what the stream holds before their
+ *     plan's upload.)
  *   - A context owns its device workspace (grown on demand, freed by
  *     qng_destroy) and, unless one was supplied, its HIP stream.  A context
  *     must not be used from two threads at once.
